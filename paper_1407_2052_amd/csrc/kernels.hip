@@ -203,8 +203,12 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
       constexpr bool SKIP_C_BARRIER = DISJ && NEXT_SPAN <= RB;
       const double c = cin[D];
       const double idx_d = B.inv_dx[D];
-      // LIM03's asymptotic-region scale 1 / (r dx_d)^2
-      const double kr = (idx_d * (1.0 / LIM03_RADIUS)) * (idx_d * (1.0 / LIM03_RADIUS));
+      // The split fluxes are held without their factor 1/2: both
+      // reconstructions are homogeneous of degree 1, so it is applied once, to
+      // the difference of the interface fluxes (a power of two: the same bits).
+      const double hidx_d = 0.5 * idx_d;
+      // LIM03's asymptotic-region scale 1 / (r dx_d)^2, for doubled data
+      const double kr = (hidx_d * (1.0 / LIM03_RADIUS)) * (hidx_d * (1.0 / LIM03_RADIUS));
 
       static_for<0, NGRP>([&](auto Gc) {
         constexpr int G = decltype(Gc)::value;
@@ -237,8 +241,8 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
           for (int vg = 0; vg < VPG; ++vg) {
             const int v = G * VPG + vg;
             if (v < NV) {
-              lds[vg * NEXTP + el] = 0.5 * fma(c, u[v], F[v]);
-              lds[(VPG + vg) * NEXTP + el] = 0.5 * fma(-c, u[v], F[v]);
+              lds[vg * NEXTP + el] = fma(c, u[v], F[v]);
+              lds[(VPG + vg) * NEXTP + el] = fma(-c, u[v], F[v]);
             }
           }
         };
@@ -510,7 +514,7 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
                 const int v = G * VPG + vg;
                 if (v < NV) {
                   const double diff = lds[RB + vg * NIFC_D + il + SI] - lds[RB + vg * NIFC_D + il];
-                  L[r][v] = fma(-diff, idx_d, L[r][v]);
+                  L[r][v] = fma(-diff, hidx_d, L[r][v]);
                 }
               }
             }
