@@ -64,6 +64,21 @@ constexpr int side_by_side(int D) {
   return 2 * VPG * (D == 0 ? XP * S::T(1) * S::T(2) : S::NEXT(D)) + (VPG + (CODES ? 1 : 0)) * S::NIFC(D);
 }
 
+// Runs per pencil of nif interfaces, for npen pencils over all variables and
+// nt threads: the split whose slowest thread does least, counting a run of r
+// interfaces as r + 2 (the differences, curvatures and limiters at its ends
+// that a neighbouring run repeats).  maxrun bounds the length.
+constexpr int runs_per_pencil(int nif, int npen, int nt, int maxrun) {
+  int best = 1, cost = 1 << 30;
+  for (int n = 1; n <= nif; ++n) {
+    const int run = (nif + n - 1) / n;
+    if ((nif + run - 1) / run != n || run > maxrun) continue;
+    const int c = (npen * n + nt - 1) / nt * (run + 2);
+    if (c < cost) { cost = c; best = n; }
+  }
+  return best;
+}
+
 template <int NDIM, bool MHD, int TX, int TY, int TZ, int NT, int NGRP, int WPE, bool EMIT = false,
           bool RUNS = false, bool LIM = false, bool GLM = false, bool HALL = false, bool CORE = false>
 __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
@@ -329,9 +344,9 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
           // interfaces.  The last run of a pencil is shifted back to end at
           // the pencil's last interface.
           constexpr int NIF = S::T(D) + 1;
-          constexpr int RUN = NIF < 5 ? NIF : 5;
-          constexpr int NRUN = (NIF + RUN - 1) / RUN;
           constexpr int NPEN = NIFC_D / NIF;
+          constexpr int NRUN = runs_per_pencil(NIF, VPG * NPEN, NT, EMIT ? 5 : NIF);
+          constexpr int RUN = (NIF + NRUN - 1) / NRUN;
           constexpr int NIT = VPG * NPEN * NRUN;
           constexpr int IPR = (NIT + NT - 1) / NT;
           double res[IPR][RUN];
