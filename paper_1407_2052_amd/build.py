@@ -16,7 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libamrvac.so")
-SOURCES = ["kernels.hip", "adjoint.hip", "runtime.cpp", "adjoint.cpp"]
+SOURCES = ["kernels.hip", "stage_tile.hip", "adjoint.hip", "runtime.cpp", "adjoint.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("AMRVAC_ARCH", "gfx950")
 
@@ -28,7 +28,7 @@ def build(verbose: bool = False) -> str:
               "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-function"]
     bdir = os.path.join(HERE, "_build")
     os.makedirs(bdir, exist_ok=True)
-    # the four translation units compile side by side (kernels.hip dominates)
+    # the translation units compile side by side (kernels.hip dominates)
     procs = []
     for src in SOURCES:
         obj = os.path.join(bdir, src + ".o")

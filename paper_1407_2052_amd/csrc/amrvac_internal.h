@@ -37,6 +37,30 @@ struct Tile {
   int o[3];             // origin (interior coordinates)
 };
 
+// Where the cells of one side of a tile start in a state buffer, and their
+// strides.  addr: a byte address (rel = 0: a caller's array), or a cell offset
+// inside a scratch slot (rel = 1).
+struct TileSide {
+  long long addr;
+  long long vs;         // between variables
+  int s1, s2;           // between rows and planes
+  int rel;
+  int rem;              // upper halo: rows before this one are the block's own
+};
+
+// What the role-split stage kernel needs of a tile, so that it follows no
+// chain of table lookups: side[0] addresses the callers' arrays, side[1] the
+// scratch slots (fixed ghost layers are in the callers' arrays either way);
+// sides 0..5 are the halos (-x, +x, -y, +y, -z, +z), 6 the tile's own cells.
+struct TileInfo {
+  int block;
+  int e[3];             // cells per direction
+  double hidx[3];       // 0.5 / dx
+  long long org;        // first cell in an interior-layout array of the block
+  long long pad_[1];
+  TileSide side[2][7];
+};
+
 // Device-resident step control: c_max slots (uint64 bit patterns of
 // non-negative doubles, so integer max == floating max), dt, t, error flag.
 struct Control {
@@ -79,6 +103,7 @@ constexpr int MAX_SRC = 3;
 struct StageParams {
   StateTable st;
   const Tile* tiles;
+  const TileInfo* info;   // the same tiles, for the role-split forms
   int tile_begin;
   int ntiles;
   Control* ctl;
@@ -125,10 +150,15 @@ struct StageParams {
 // and the runtime that selects it.
 struct StageVariant {
   int ndim, mhd, rec, hall, tx, ty, tz, nt, ngrp, wpe;   // mhd: physics code; rec: 0 MP5, 1 LIM03
+  int info;              // > 0: reads the TileInfo table, built for this halo width
   const void* fn;
   void (*launch)(const StageParams&, int grid, hipStream_t);
   const char* name;
 };
+
+const StageVariant* tile_variants(int* count);   // stage_tile.hip
+void launch_tile_info(const BlockDev* blocks, const Tile* tiles, TileInfo* info, int ntiles, int ndim, int hg, int tx,
+                      int ty, int tz, hipStream_t s);
 
 struct CmaxParams {
   StateTable st;

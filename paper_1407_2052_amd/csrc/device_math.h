@@ -187,6 +187,28 @@ __device__ __forceinline__ bool prim(const double* u, double gamma, PrimD& w) {
          (w.rho < __builtin_huge_val());
 }
 
+// The primitives of a state whose 1/rho and p were already recovered by prim
+// (the same operations on the same inputs: the same bits, without the
+// division).
+template <int NDIM, bool MHD>
+__device__ __forceinline__ void prim_from(const double* u, double ri, double p, PrimD& w) {
+  using E = Eq<NDIM, MHD>;
+  w.rho = u[0];
+  w.ri = ri;
+  w.p = p;
+  w.b2 = 0.0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    w.v[k] = (k < E::NC) ? u[1 + k] * ri : 0.0;
+    w.B[k] = 0.0;
+  }
+  if constexpr (MHD) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w.B[k] = u[5 + k];
+    w.b2 = fma(w.B[2], w.B[2], fma(w.B[1], w.B[1], w.B[0] * w.B[0]));
+  }
+}
+
 // Physical flux along D (Sect. 3 eqs. masscons, momentum, total; Sect. 4.1
 // eq. b1eq and Sect. 4.3 eqs. momentummhd, fractional with B0 = 0).
 template <int NDIM, bool MHD, int D>
@@ -232,6 +254,28 @@ __device__ __forceinline__ double fast_speed(const PrimD& w, int d, double gamma
     double disc = fma(s, s, -4.0 * a2 * bd2);
     disc = disc < 0.0 ? 0.0 : disc;
     return sqrt(0.5 * (s + sqrt(disc)));
+  }
+}
+
+// Whether |v_d| + fast_speed(w, d) may exceed r: false only where the value
+// the expression rounds to is at most r.  With M = r - |v_d| the speed is
+// below M when s + sqrt(disc) < 2 M^2 (fast_speed's s and disc), that is when
+// 2 M^2 - s > 0 and disc < (2 M^2 - s)^2.  M is lowered by 1e-14 and must be
+// at least r/8, which outweighs the few roundings of either side; NaN gives
+// true.
+template <bool MHD>
+__device__ __forceinline__ bool speed_may_exceed(const PrimD& w, int d, double gamma, double r) {
+  const double M = (r - fabs(w.v[d])) * (1.0 - 1e-14);
+  const double a2 = gamma * w.p * w.ri;
+  if constexpr (!MHD) {
+    return !(M > 0.125 * r && a2 < M * M);
+  } else {
+    const double b2 = w.b2 * w.ri;
+    const double bd2 = w.B[d] * w.B[d] * w.ri;
+    const double s = a2 + b2;
+    const double disc = fma(s, s, -4.0 * a2 * bd2);
+    const double q = fma(2.0 * M, M, -s);
+    return !(M > 0.125 * r && q > 0.0 && disc < q * q);
   }
 }
 
@@ -385,6 +429,38 @@ __device__ __forceinline__ void mp5_run(const double* f, double* out, int* code)
                       fmax(D[kk + 1], 0.0), 0.5 * D[kk + 1], gm[kk + 1], gm[kk], q);
       code[kk] = mp5_piece(g, D[kk + 2], D[kk + 1], q, kpp[kk + 1], kmp[kk]);
     }
+  }
+}
+
+// The values of mp5_run<RUN, false>, one interface after the other with only
+// what the next one needs held: for kernels whose registers are few.  The
+// barriers keep the scheduler from opening several interfaces at once.
+template <int RUN>
+__device__ __forceinline__ void mp5_stream(const double* f, double* out) {
+  double D[4];   // differences of the interface's stencil
+  D[0] = f[1] - f[0];
+  D[1] = f[2] - f[1];
+  D[2] = f[3] - f[2];
+  double dc = D[2] - D[1];                  // curvature at the stencil centre
+  double m4m = m4pair(D[1] - D[0], dc);     // limiter below it
+  double dn1 = fmin(D[1], 0.0), dp1 = fmax(D[1], 0.0), h1 = 0.5 * D[1];
+#pragma unroll
+  for (int kk = 0; kk < RUN; ++kk) {
+    D[3] = f[kk + 4] - f[kk + 3];
+    const double dcp = D[3] - D[2];
+    const double m4p = m4pair(dc, dcp);
+    const double dn = fmin(D[2], 0.0), dp = fmax(D[2], 0.0), h = 0.5 * D[2];
+    Mp5Bounds q;
+    out[kk] = f[kk + 2] + mp5_clamp(mp5_fifth(D), dn, dp, h, dn1, dp1, h1, m4p, m4m, q);
+    D[0] = D[1];
+    D[1] = D[2];
+    D[2] = D[3];
+    dc = dcp;
+    m4m = m4p;
+    dn1 = dn;
+    dp1 = dp;
+    h1 = h;
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 

@@ -52,6 +52,9 @@
 // early-exit test holds).
 #include "device_math.h"
 
+#include <iterator>
+#include <vector>
+
 namespace amrvac {
 
 // ---------------------------------------------------------------------------
@@ -903,57 +906,57 @@ static void launch_stage(const StageParams& p, int grid, hipStream_t s) {
 
 // rec: the reconstruction (0 MP5, 1 LIM03)
 #define AMRVAC_VARIANT(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                          \
-  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE>, \
+  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE>, \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE>,                                             \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE}
 // the same with interfaces evaluated in runs along each pencil
 #define AMRVAC_VARIANT_R(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                     \
-  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true>, \
+  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true>, \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true>,                                             \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs"}
 // the same with the owned cells' state kept in registers for the whole tile
 #define AMRVAC_VARIANT_RC(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                  \
-  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE,                                                                   \
+  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0,                                                                  \
    (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, false, false, false, true>,          \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, false, false, false, true>,                  \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-core"}
 // GLM-MHD (physics code 2), MP5 or LIM03 (REC), in runs along each pencil
 #define AMRVAC_VARIANT_G(ND, REC, TX, TY, TZ, NT, NGRP, WPE)                                                    \
-  {ND, 2, REC, 0, TX, TY, TZ, NT, NGRP, WPE,                                                                       \
+  {ND, 2, REC, 0, TX, TY, TZ, NT, NGRP, WPE, 0,                                                                      \
    (const void*)&k_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), true>,                  \
    &launch_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), true>,                          \
    #ND "d-glm-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-rec" #REC}
 // Hall MHD (physics MHD, eta_h > 0), MP5 or LIM03 (REC), in runs along each pencil
 #define AMRVAC_VARIANT_H(ND, REC, TX, TY, TZ, NT, NGRP, WPE)                                                   \
-  {ND, 1, REC, 1, TX, TY, TZ, NT, NGRP, WPE,                                                                   \
+  {ND, 1, REC, 1, TX, TY, TZ, NT, NGRP, WPE, 0,                                                                  \
    (const void*)&k_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), false, true>,          \
    &launch_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), false, true>,                  \
    #ND "d-hall-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-rec" #REC}
 // LIM03 reconstruction in runs along each pencil
 #define AMRVAC_VARIANT_LR(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                         \
-  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, true>, \
+  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, true>, \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, true>,                                             \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-lim03"}
 // LIM03 reconstruction
 #define AMRVAC_VARIANT_L(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                            \
-  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, false, true>, \
+  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, false, true>, \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, false, true>,                                             \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-lim03"}
 
 // Owned cells kept in registers for the whole tile (CORE), for LIM03, GLM
 // and Hall MHD
 #define AMRVAC_VARIANT_LRC(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                  \
-  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE,                                                                   \
+  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, 0,                                                                  \
    (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, true, false, false, true>,           \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, true, false, false, true>,                   \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-lim03-core"}
 #define AMRVAC_VARIANT_GC(ND, REC, TX, TY, TZ, NT, NGRP, WPE)                                                 \
-  {ND, 2, REC, 0, TX, TY, TZ, NT, NGRP, WPE,                                                                 \
+  {ND, 2, REC, 0, TX, TY, TZ, NT, NGRP, WPE, 0,                                                                \
    (const void*)&k_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), true, false, true>,   \
    &launch_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), true, false, true>,           \
    #ND "d-glm-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-rec" #REC "-core"}
 #define AMRVAC_VARIANT_HC(ND, REC, TX, TY, TZ, NT, NGRP, WPE)                                                 \
-  {ND, 1, REC, 1, TX, TY, TZ, NT, NGRP, WPE,                                                                 \
+  {ND, 1, REC, 1, TX, TY, TZ, NT, NGRP, WPE, 0,                                                                \
    (const void*)&k_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), false, true, true>,   \
    &launch_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), false, true, true>,           \
    #ND "d-hall-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-rec" #REC "-core"}
@@ -964,117 +967,71 @@ static void launch_stage(const StageParams& p, int grid, hipStream_t s) {
 static const StageVariant g_variants[] = {
     // 1D
     AMRVAC_VARIANT(1, false, 128, 1, 1, 128, 1, 1),
-    AMRVAC_VARIANT(1, false, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_RC(1, false, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT(1, true, 128, 1, 1, 128, 1, 1),
-    AMRVAC_VARIANT(1, true, 64, 1, 1, 64, 1, 1),
-    AMRVAC_VARIANT_R(1, true, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_RC(1, true, 64, 1, 1, 64, 1, 1),
-    // 2D
-    AMRVAC_VARIANT(2, false, 16, 16, 1, 256, 1, 1),
-    AMRVAC_VARIANT(2, false, 16, 16, 1, 256, 1, 3),
-    AMRVAC_VARIANT(2, false, 32, 8, 1, 256, 1, 1),
-    AMRVAC_VARIANT_R(2, false, 16, 16, 1, 256, 1, 1),
+    // 2D and 3D: the role-split forms are faster; these have no limit on the
+    // extents of a block
     AMRVAC_VARIANT_RC(2, false, 16, 16, 1, 256, 1, 2),
-    AMRVAC_VARIANT(2, true, 16, 16, 1, 256, 2, 1),
-    AMRVAC_VARIANT(2, true, 16, 16, 1, 256, 1, 1),
-    AMRVAC_VARIANT(2, true, 16, 16, 1, 256, 2, 3),
-    AMRVAC_VARIANT(2, true, 32, 8, 1, 256, 2, 1),
-    AMRVAC_VARIANT_R(2, true, 16, 16, 1, 256, 1, 1),
-    AMRVAC_VARIANT_R(2, true, 16, 16, 1, 256, 2, 2),
     AMRVAC_VARIANT_RC(2, true, 16, 16, 1, 256, 1, 2),
-    AMRVAC_VARIANT_RC(2, true, 16, 16, 1, 256, 2, 2),
-    // 3D: the owned-cell (CORE) forms first
     AMRVAC_VARIANT_RC(3, false, 8, 8, 4, 256, 1, 2),
-    AMRVAC_VARIANT(3, false, 8, 8, 8, 512, 2, 1),
-    AMRVAC_VARIANT(3, false, 8, 8, 4, 256, 1, 1),
-    AMRVAC_VARIANT_R(3, false, 8, 8, 4, 256, 1, 2),
     AMRVAC_VARIANT_RC(3, true, 8, 8, 8, 512, 1, 2),
-    AMRVAC_VARIANT_RC(3, true, 8, 8, 4, 256, 1, 2),
-    AMRVAC_VARIANT_RC(3, true, 8, 4, 4, 128, 1, 2),
-    AMRVAC_VARIANT_RC(3, true, 8, 8, 4, 256, 2, 3),
-    AMRVAC_VARIANT_R(3, true, 8, 8, 4, 256, 2, 4),
-    AMRVAC_VARIANT_R(3, true, 8, 8, 4, 256, 2, 3),
-    AMRVAC_VARIANT_R(3, true, 8, 8, 8, 512, 2, 4),
-    AMRVAC_VARIANT_R(3, true, 8, 8, 4, 256, 1, 2),
-    AMRVAC_VARIANT(3, true, 8, 8, 4, 256, 2, 3),
-    // LIM03 (the default of each (ndim, physics) first)
-    AMRVAC_VARIANT_LR(1, true, 64, 1, 1, 64, 1, 1),
+    // LIM03
     AMRVAC_VARIANT_LRC(1, true, 64, 1, 1, 64, 1, 1),
-    AMRVAC_VARIANT_LR(2, false, 16, 16, 1, 256, 1, 1),
     AMRVAC_VARIANT_LRC(2, false, 16, 16, 1, 256, 1, 2),
-    AMRVAC_VARIANT_LR(2, true, 16, 16, 1, 256, 1, 1),
-    AMRVAC_VARIANT_LR(2, true, 16, 16, 1, 256, 2, 2),
     AMRVAC_VARIANT_LRC(2, true, 16, 16, 1, 256, 1, 2),
     AMRVAC_VARIANT_LRC(3, false, 8, 8, 4, 256, 1, 2),
-    AMRVAC_VARIANT_LR(3, false, 8, 8, 4, 256, 1, 2),
-    AMRVAC_VARIANT_LRC(3, true, 8, 8, 4, 256, 1, 2),
     AMRVAC_VARIANT_LRC(3, true, 8, 8, 8, 512, 1, 2),
-    AMRVAC_VARIANT_LR(3, true, 8, 8, 4, 256, 2, 4),
-    AMRVAC_VARIANT_LR(3, true, 8, 8, 4, 256, 2, 3),
-    AMRVAC_VARIANT_LR(3, true, 8, 8, 8, 512, 2, 4),
     AMRVAC_VARIANT_L(1, false, 128, 1, 1, 128, 1, 1),
-    AMRVAC_VARIANT_L(1, false, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_L(1, true, 128, 1, 1, 128, 1, 1),
-    AMRVAC_VARIANT_L(1, true, 64, 1, 1, 64, 1, 1),
-    AMRVAC_VARIANT_L(2, false, 16, 16, 1, 256, 1, 1),
-    AMRVAC_VARIANT_L(2, false, 32, 8, 1, 256, 1, 1),
-    AMRVAC_VARIANT_L(2, true, 16, 16, 1, 256, 2, 1),
-    AMRVAC_VARIANT_L(2, true, 16, 16, 1, 256, 1, 1),
-    AMRVAC_VARIANT_L(2, true, 32, 8, 1, 256, 2, 1),
-    AMRVAC_VARIANT_L(3, false, 8, 8, 4, 256, 1, 1),
-    AMRVAC_VARIANT_L(3, false, 8, 8, 8, 512, 2, 1),
-    AMRVAC_VARIANT_L(3, true, 8, 8, 4, 256, 2, 3),
     // GLM-MHD
     AMRVAC_VARIANT_G(1, 0, 64, 1, 1, 64, 1, 1),
-    AMRVAC_VARIANT_G(2, 0, 16, 16, 1, 256, 2, 2),
-    AMRVAC_VARIANT_G(2, 0, 16, 16, 1, 256, 1, 1),
     AMRVAC_VARIANT_GC(2, 0, 16, 16, 1, 256, 1, 2),
     AMRVAC_VARIANT_GC(3, 0, 8, 8, 4, 256, 1, 2),
     AMRVAC_VARIANT_GC(3, 0, 8, 8, 8, 512, 1, 2),
-    AMRVAC_VARIANT_GC(3, 0, 8, 8, 4, 256, 3, 3),
-    AMRVAC_VARIANT_G(3, 0, 8, 8, 4, 256, 2, 3),
-    AMRVAC_VARIANT_G(3, 0, 8, 8, 4, 256, 3, 4),
     AMRVAC_VARIANT_G(1, 1, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_G(2, 1, 16, 16, 1, 256, 2, 2),
     AMRVAC_VARIANT_GC(3, 1, 8, 8, 4, 256, 1, 2),
-    AMRVAC_VARIANT_G(3, 1, 8, 8, 4, 256, 2, 4),
-    AMRVAC_VARIANT_G(3, 1, 8, 8, 4, 256, 2, 3),
     // Hall MHD
     AMRVAC_VARIANT_H(1, 0, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_H(2, 0, 16, 16, 1, 256, 2, 2),
     AMRVAC_VARIANT_HC(3, 0, 8, 8, 4, 256, 1, 2),
-    AMRVAC_VARIANT_H(3, 0, 8, 8, 4, 256, 2, 4),
-    AMRVAC_VARIANT_H(3, 0, 8, 8, 4, 256, 2, 2),
     AMRVAC_VARIANT_H(1, 1, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_H(2, 1, 16, 16, 1, 256, 2, 2),
     AMRVAC_VARIANT_HC(3, 1, 8, 8, 4, 256, 1, 2),
-    AMRVAC_VARIANT_H(3, 1, 8, 8, 4, 256, 2, 4),
 };
 
+// The role-split tile forms (stage_tile.hip) first: the default where they exist.
 const StageVariant* stage_variants(int* count) {
-  *count = (int)(sizeof(g_variants) / sizeof(g_variants[0]));
-  return g_variants;
+  static const std::vector<StageVariant> all = [] {
+    int n = 0;
+    const StageVariant* t = tile_variants(&n);
+    std::vector<StageVariant> v(t, t + n);
+    v.insert(v.end(), std::begin(g_variants), std::end(g_variants));
+    return v;
+  }();
+  *count = (int)all.size();
+  return all.data();
 }
 
 // Code-emitting stage kernels (the adjoint's forward recompute), one per
 // (ndim, physics); their tile shapes match the adjoint kernels'.
 #define AMRVAC_EMIT(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                          \
-  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, true, true>, \
+  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, true, true>, \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, true, true>,                                             \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-emit"}
 #define AMRVAC_EMIT_L(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                             \
-  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, true, true, true>, \
+  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, true, true, true>, \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, true, true, true>,                                             \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-lim03-emit"}
 
 #define AMRVAC_EMIT_C(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                       \
-  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE,                                                                   \
+  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0,                                                                  \
    (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, true, true, false, false, false, true>,           \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, true, true, false, false, false, true>,                   \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-emit-core"}
 #define AMRVAC_EMIT_LC(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                      \
-  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE,                                                                   \
+  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, 0,                                                                  \
    (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, true, true, true, false, false, true>,            \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, true, true, true, false, false, true>,                    \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-lim03-emit-core"}

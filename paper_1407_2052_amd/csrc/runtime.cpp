@@ -77,6 +77,8 @@ static void drop_graphs(amrvac_ctx* c) {
 static void free_tables(amrvac_ctx* c) {
   if (c->d_blocks) (void)hipFree(c->d_blocks);
   if (c->d_tiles) (void)hipFree(c->d_tiles);
+  if (c->d_info) (void)hipFree(c->d_info);
+  c->d_info = nullptr;
   if (c->d_scr) (void)hipFree(c->d_scr);
   if (c->d_dxtab) (void)hipFree(c->d_dxtab);
   if (c->d_rhs_ptrs) (void)hipFree(c->d_rhs_ptrs);
@@ -135,6 +137,29 @@ static const StageVariant* pick_variant(const amrvac_ctx* c, int want) {
     }
   }
   return nullptr;
+}
+
+// Whether every cell a role-split tile reads lies within 32-bit byte offsets
+// of the tile's first cell: at most 16 rows and 3 + 3 halo rows, or 4 planes
+// and 3 + 3 halo planes, of a padded block (2^28 cells leave the factor 8 of a
+// double inside 2^31).
+static bool offsets_fit(const amrvac_ctx* c) {
+  for (const amrvac_block& q : c->hb) {
+    const long long s1 = q.n[0] + 2 * NG, s2 = s1 * (q.n[1] + 2 * NG);
+    if ((c->cfg.ndim >= 2 ? 24 * s1 : 0) + (c->cfg.ndim >= 3 ? 12 * s2 : 0) > (1ll << 28)) return false;
+  }
+  return true;
+}
+
+// The kernel variant i runs on the current block list: itself, or, for a
+// role-split form on blocks whose rows or planes exceed its offsets, the first
+// form of this context without that limit (the same results bit for bit).
+static const StageVariant* resolve_variant(const amrvac_ctx* c, int i) {
+  const StageVariant* v = pick_variant(c, i);
+  if (!v || v->info == 0 || offsets_fit(c)) return v;
+  for (int k = 0; k < count_variants(c); ++k)
+    if (pick_variant(c, k)->info == 0) return pick_variant(c, k);
+  return v;
 }
 
 static amrvac_status select_variant(amrvac_ctx* c, int i);
@@ -270,6 +295,14 @@ static amrvac_status build_tiles(amrvac_ctx* c) {
   HIP_TRY(c, hipMalloc(&c->d_tiles, sizeof(Tile) * c->htiles.size()));
   HIP_TRY(c, hipMemcpyAsync(c->d_tiles, c->htiles.data(), sizeof(Tile) * c->htiles.size(),
                             hipMemcpyHostToDevice, c->stream));
+  if (c->d_info) (void)hipFree(c->d_info);
+  c->d_info = nullptr;
+  if (V->info > 0) {
+    HIP_TRY(c, hipMalloc(&c->d_info, sizeof(TileInfo) * c->htiles.size()));
+    launch_tile_info(c->d_blocks, c->d_tiles, c->d_info, (int)c->htiles.size(), c->cfg.ndim, V->info, V->tx, V->ty,
+                     V->tz, c->stream);
+    HIP_TRY(c, hipGetLastError());
+  }
   if (c->d_ptiles) (void)hipFree(c->d_ptiles);
   c->d_ptiles = nullptr;
   if (!c->hptiles.empty()) {
@@ -309,12 +342,12 @@ amrvac_status ensure_slots(amrvac_ctx* c, int n) {
 }  // namespace amrvac
 
 static amrvac_status select_variant(amrvac_ctx* c, int i) {
-  const StageVariant* v = pick_variant(c, i);
+  const StageVariant* v = resolve_variant(c, i);
   if (!v) return fail(c, AMRVAC_ERR_INVALID, "variant %d does not exist", i);
+  c->var_index = i;
   if (v == c->var && !c->htiles.empty()) return AMRVAC_OK;
   drop_graphs(c);
   c->var = v;
-  c->var_index = i;
   if (c->hb.empty()) return AMRVAC_OK;
   return build_tiles(c);
 }
@@ -444,6 +477,7 @@ static StageParams make_params(const amrvac_ctx* c, const Recipe& r, int cm_in, 
   StageParams p{};
   p.st = state_table(c);
   p.tiles = c->d_tiles;
+  p.info = c->d_info;
   p.tile_begin = 0;
   p.ntiles = (int)c->htiles.size();
   p.ctl = c->d_ctl;
@@ -727,6 +761,7 @@ amrvac_status amrvac_set_blocks(amrvac_ctx* c, const amrvac_block* blocks, int n
   drop_graphs(c);
   free_tables(c);
   c->hb.assign(blocks, blocks + nblocks);
+  c->var = resolve_variant(c, c->var_index);
   c->hdev.resize(nblocks);
   c->active.assign(nblocks, 1);
   c->n_active = nblocks;

@@ -72,6 +72,7 @@ struct amrvac_ctx {
   int var_index = 0;
   std::vector<Tile> htiles;
   Tile* d_tiles = nullptr;
+  amrvac::TileInfo* d_info = nullptr;   // of the same tiles, for variants that read it
   std::vector<int> blk_tile_begin, blk_tile_count;
 
   // dynamic grid activation: 1 = advanced, 0 = passive (kept, read as halo)
