@@ -342,7 +342,7 @@ extern "C" amrvac_status amrvac_ssprk_adjoint(amrvac_ctx* c, int scheme, double 
   launch_set_control(c->d_ctl, dt, 0.4, 0.0, c->stream);
   int cur = 0;
   const int last_needed = (M - 1) * k;   // states beyond the last checkpoint are not needed
-  if (last_needed > 0) launch_cmax_of(c, cur, 0, c->stream);
+  if (last_needed > 0) launch_cmax_of(c, cur, 0, c->stream, true);
   for (int n = 0; n < last_needed; ++n) {
     int nxt;
     if ((n + 1) % k == 0) {

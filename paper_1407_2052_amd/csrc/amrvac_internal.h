@@ -57,14 +57,26 @@ struct TileInfo {
   int e[3];             // cells per direction
   double hidx[3];       // 0.5 / dx
   long long org;        // first cell in an interior-layout array of the block
-  long long pad_[1];
+  long long pad_[2];    // to 64 bytes
   TileSide side[2][7];
+};
+
+// c_max slots are spread over CM_SUBS partial maxima in cache lines of their
+// own (work-group w adds to part w mod CM_SUBS), which every reader folds:
+// atomics to one line are served one after the other, about 11 ns each, and a
+// launch ends with up to three per work-group (2048 work-groups of the
+// stand-alone reduction took 75 us for 0.5 M cells, 512 of a stage 17 us at
+// its end).
+constexpr int CM_SUBS = 32;
+struct CmaxPart {
+  unsigned long long v[3];
+  unsigned long long pad_[5];
 };
 
 // Device-resident step control: c_max slots (uint64 bit patterns of
 // non-negative doubles, so integer max == floating max), dt, t, error flag.
 struct Control {
-  unsigned long long cm[MAX_SLOTS][3];
+  CmaxPart cm[MAX_SLOTS][CM_SUBS];
   double dt;
   double t;
   double dt_fixed;      // > 0: fixed step

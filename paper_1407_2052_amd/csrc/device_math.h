@@ -559,9 +559,80 @@ struct TileSchedule {
   }
 };
 
-__device__ __forceinline__ double wave_max(double x) {
+// The value of another lane, for reductions over a wavefront without the LDS
+// pipe and without per-lane addresses (which would be held in registers):
+// steps 0..3 rotate the 16 lanes of a row by 8, 4, 2, 1, step 4 pairs the rows
+// of a half, step 5 the halves.  Combining a value with its partner of every
+// step gives each lane the reduction over all 64.
+template <int STEP>
+__device__ __forceinline__ unsigned long long partner_bits(unsigned long long x) {
+  const unsigned lo = (unsigned)x, hi = (unsigned)(x >> 32);
+  unsigned a, b;
+  if constexpr (STEP < 4) {
+    constexpr int CTRL = 0x120 + (8 >> STEP);   // row_ror
+    a = (unsigned)__builtin_amdgcn_update_dpp(0, (int)lo, CTRL, 0xf, 0xf, false);
+    b = (unsigned)__builtin_amdgcn_update_dpp(0, (int)hi, CTRL, 0xf, 0xf, false);
+  } else {
+    // a swap of x with itself leaves one partner's rows in each result: the
+    // rows that were replaced hold the partner, the others x itself
+    const bool upper = STEP == 4 ? (threadIdx.x & 16) != 0 : (threadIdx.x & 32) != 0;
+    if constexpr (STEP == 4) {
+      const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+      const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+      a = upper ? l[0] : l[1];
+      b = upper ? h[0] : h[1];
+    } else {
+      const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+      const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+      a = upper ? l[0] : l[1];
+      b = upper ? h[0] : h[1];
+    }
+  }
+  return ((unsigned long long)b << 32) | a;
+}
+
+// c_max of a slot, per direction (0 for inactive ones): the maximum over its
+// parts, formed by every wavefront for itself (all lanes active).
+template <int NDIM>
+__device__ __forceinline__ void load_cmax(const Control* ctl, int slot, double* c) {
+  const CmaxPart* p = &ctl->cm[slot][threadIdx.x & (CM_SUBS - 1)];
+  unsigned long long x[3] = {0ull, 0ull, 0ull};
 #pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) x = fmax(x, __shfl_xor(x, m, 64));
+  for (int d = 0; d < NDIM; ++d) x[d] = p->v[d];
+  static_assert(CM_SUBS == 32, "one part per lane of a half wavefront");
+  static_for<0, 5>([&](auto Step) {
+#pragma unroll
+    for (int d = 0; d < NDIM; ++d) {
+      const unsigned long long y = partner_bits<decltype(Step)::value>(x[d]);
+      x[d] = y > x[d] ? y : x[d];
+    }
+  });
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)x[d]);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(x[d] >> 32));
+    c[d] = __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+  }
+}
+
+// Folds a work-group's maximum along d into a slot.
+__device__ __forceinline__ void fold_cmax(Control* ctl, int slot, int d, double m) {
+  atomicMax(&ctl->cm[slot][blockIdx.x & (CM_SUBS - 1)].v[d], (unsigned long long)__double_as_longlong(m));
+}
+
+// Clears a slot (the first CM_SUBS threads of the calling work-group).
+__device__ __forceinline__ void clear_cmax(Control* ctl, int slot) {
+  if (threadIdx.x < CM_SUBS) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) ctl->cm[slot][threadIdx.x].v[d] = 0ull;
+  }
+}
+
+__device__ __forceinline__ double wave_max(double x) {
+  static_for<0, 6>([&](auto Step) {
+    x = fmax(x, __longlong_as_double(
+                    (long long)partner_bits<decltype(Step)::value>((unsigned long long)__double_as_longlong(x))));
+  });
   return x;
 }
 

@@ -136,8 +136,11 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
   const double gamma = P.gamma;
 
   double cin[3];
+  load_cmax<NDIM>(ctl, P.cm_in, cin);
+  if (EMIT && P.cm_hist && blockIdx.x == 0 && tid == 0) {
 #pragma unroll
-  for (int d = 0; d < 3; ++d) cin[d] = __longlong_as_double((long long)ctl->cm[P.cm_in][d]);
+    for (int d = 0; d < 3; ++d) P.cm_hist[d] = cin[d];
+  }
   if constexpr (GLM) {
     // the cleaning speed c_h = max_d c_max,d serves every direction
     double ch = cin[0];
@@ -150,14 +153,7 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
   const double psi_decay = (GLM && P.decay_psi) ? ctl->psi_decay : 1.0;
   const double dtb = dt * P.b;
   const double dtsb = dt * P.sb;
-  if (EMIT && P.cm_hist && blockIdx.x == 0 && tid == 0) {
-#pragma unroll
-    for (int d = 0; d < 3; ++d) P.cm_hist[d] = __longlong_as_double((long long)ctl->cm[P.cm_in][d]);
-  }
-  if (P.cm_reset >= 0 && blockIdx.x == 0 && tid == 0) {
-#pragma unroll
-    for (int d = 0; d < 3; ++d) ctl->cm[P.cm_reset][d] = 0ull;
-  }
+  if (P.cm_reset >= 0 && blockIdx.x == 0) clear_cmax(ctl, P.cm_reset);
 
   double run[3] = {0.0, 0.0, 0.0};
   bool ok_all = true;
@@ -675,7 +671,7 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
       for (int d = 0; d < NDIM; ++d) {
         double m = red[0][d];
         for (int q = 1; q < NT / 64; ++q) m = fmax(m, red[q][d]);
-        atomicMax(&ctl->cm[P.cm_out][d], (unsigned long long)__double_as_longlong(m));
+        fold_cmax(ctl, P.cm_out, d, m);
       }
     }
   }
@@ -729,23 +725,25 @@ __global__ void __launch_bounds__(256) k_cmax(CmaxParams P) {
   if (tid == 0) {
     for (int d = 0; d < NDIM; ++d) {
       double m = fmax(fmax(red[0][d], red[1][d]), fmax(red[2][d], red[3][d]));
-      atomicMax(&P.ctl->cm[P.slot][d], (unsigned long long)__double_as_longlong(m));
+      fold_cmax(P.ctl, P.slot, d, m);
     }
   }
   if (!ok_all) atomicOr(&P.ctl->err, 1);
 }
 
 // dt from c_max (or the fixed step), t += dt, and clearing of the c_max
-// slots the coming stages accumulate into.  One thread.
-__global__ void k_step_begin(Control* ctl, const double* dxtab, int ndim, int glm, int clear_lo,
-                             int clear_hi) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// slots the coming stages accumulate into.  One wavefront.
+template <int NDIM>
+__global__ void __launch_bounds__(64) k_step_begin(Control* ctl, const double* dxtab, int glm, int clear_lo,
+                                                 int clear_hi) {
   double cm[3];
-  for (int d = 0; d < 3; ++d) cm[d] = __longlong_as_double((long long)ctl->cm[0][d]);
+  load_cmax<NDIM>(ctl, 0, cm);
+  for (int s = clear_lo; s <= clear_hi; ++s) clear_cmax(ctl, s);
+  if (threadIdx.x != 0) return;
   double ch = cm[0];
   if (glm) {   // every direction moves at the cleaning speed c_h = max_d c_max,d
-    for (int d = 1; d < ndim; ++d) ch = fmax(ch, cm[d]);
-    for (int d = 0; d < ndim; ++d) cm[d] = ch;
+    for (int d = 1; d < NDIM; ++d) ch = fmax(ch, cm[d]);
+    for (int d = 0; d < NDIM; ++d) cm[d] = ch;
   }
   double dt;
   if (ctl->dt_fixed > 0.0) {
@@ -754,7 +752,7 @@ __global__ void k_step_begin(Control* ctl, const double* dxtab, int ndim, int gl
     double worst = 0.0;
     for (int q = 0; q < ctl->ndx; ++q) {
       double s = 0.0;
-      for (int d = 0; d < ndim; ++d) s = s + cm[d] / dxtab[3 * q + d];
+      for (int d = 0; d < NDIM; ++d) s = s + cm[d] / dxtab[3 * q + d];
       worst = fmax(worst, s);
     }
     dt = ctl->cfl / worst;
@@ -762,12 +760,12 @@ __global__ void k_step_begin(Control* ctl, const double* dxtab, int ndim, int gl
   ctl->dt = dt;
   ctl->psi_decay = glm ? exp((-dt / GLM_CR) * ch) : 1.0;
   ctl->t += dt;
-  for (int s = clear_lo; s <= clear_hi; ++s)
-    for (int d = 0; d < 3; ++d) ctl->cm[s][d] = 0ull;
 }
 
 // Host-provided step controls, set on the stream (no host buffer lifetime).
-__global__ void k_set_control(Control* ctl, double dt_fixed, double cfl, double t) {
+// Also clears the c_max slot of the coming reduction of the initial state.
+__global__ void __launch_bounds__(64) k_set_control(Control* ctl, double dt_fixed, double cfl, double t) {
+  clear_cmax(ctl, 0);
   if (threadIdx.x == 0 && blockIdx.x == 0) {
     ctl->dt_fixed = dt_fixed;
     ctl->cfl = cfl;
@@ -890,7 +888,7 @@ __global__ void __launch_bounds__(256) k_sum_fixed(const double* x, int n, doubl
 
 // Clears one c_max slot (used before a standalone c_max reduction).
 __global__ void k_clear_slot(Control* ctl, int slot) {
-  if (threadIdx.x < 3 && blockIdx.x == 0) ctl->cm[slot][threadIdx.x] = 0ull;
+  clear_cmax(ctl, slot);
 }
 
 // ---------------------------------------------------------------------------
@@ -1070,7 +1068,9 @@ void launch_cmax(int ndim, int mhd, const CmaxParams& p, int grid, hipStream_t s
 
 void launch_step_begin(Control* ctl, const double* dxtab, int ndim, int glm, int clear_lo, int clear_hi,
                        hipStream_t s) {
-  hipLaunchKernelGGL(k_step_begin, dim3(1), dim3(64), 0, s, ctl, dxtab, ndim, glm, clear_lo, clear_hi);
+  if (ndim == 1) hipLaunchKernelGGL(k_step_begin<1>, dim3(1), dim3(64), 0, s, ctl, dxtab, glm, clear_lo, clear_hi);
+  if (ndim == 2) hipLaunchKernelGGL(k_step_begin<2>, dim3(1), dim3(64), 0, s, ctl, dxtab, glm, clear_lo, clear_hi);
+  if (ndim == 3) hipLaunchKernelGGL(k_step_begin<3>, dim3(1), dim3(64), 0, s, ctl, dxtab, glm, clear_lo, clear_hi);
 }
 
 void launch_set_control(Control* ctl, double dt_fixed, double cfl, double t, hipStream_t s) {

@@ -547,7 +547,7 @@ static void launch_stage(amrvac_ctx* c, StageParams p, int exec, hipStream_t s) 
 }
 
 namespace amrvac {
-void launch_cmax_of(amrvac_ctx* c, int buf, int slot, hipStream_t s) {
+void launch_cmax_of(amrvac_ctx* c, int buf, int slot, hipStream_t s, bool cleared) {
   CmaxParams q{};
   q.st = state_table(c);
   q.tiles = c->d_tiles;
@@ -560,7 +560,7 @@ void launch_cmax_of(amrvac_ctx* c, int buf, int slot, hipStream_t s) {
   q.in = buf;
   q.slot = slot;
   q.eta_h = c->cfg.eta_h;
-  launch_clear_slot(c->d_ctl, slot, s);
+  if (!cleared) launch_clear_slot(c->d_ctl, slot, s);
   int grid = (int)std::min<long long>((long long)c->ncu * 8, (long long)c->htiles.size());
   // psi enters no wave speed: GLM uses the MHD reduction
   launch_cmax(c->cfg.ndim, c->cfg.physics != AMRVAC_HD, q, grid, s);
@@ -911,7 +911,7 @@ amrvac_status amrvac_autotune(amrvac_ctx* c, int scheme, int nsteps, double* ms_
     launch_copy_interior(state_table(c), c->d_tiles, (int)c->htiles.size(), c->var->tx, c->var->ty, c->var->tz,
                          c->nvar, 0, 4, std::min<int>(c->ncu * 8, (int)c->htiles.size()), c->stream);
     launch_set_control(c->d_ctl, 0.0, 0.4, 0.0, c->stream);
-    launch_cmax_of(c, 4, 0, c->stream);
+    launch_cmax_of(c, 4, 0, c->stream, true);
     enqueue_step(c, scheme, AMRVAC_EXEC_BATCHED, c->stream, 4, 1, 2, 3, 4);   // warm-up
     HIP_TRY(c, hipEventRecord(e0, c->stream));
     for (int it = 0; it < nsteps; ++it) enqueue_step(c, scheme, AMRVAC_EXEC_BATCHED, c->stream, 4, 1, 2, 3, 4);
@@ -961,12 +961,14 @@ amrvac_status amrvac_fd_rhs(amrvac_ctx* c, double* const* rhs, double* cmax_out)
   launch_stage(c, p, c->exec, c->stream);
   HIP_TRY(c, hipGetLastError());
   if (cmax_out) {
-    unsigned long long cm[3];
+    CmaxPart cm[CM_SUBS];
     HIP_TRY(c, hipMemcpyAsync(cm, c->d_ctl->cm[0], sizeof(cm), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     for (int d = 0; d < 3; ++d) {
+      unsigned long long bits = 0;
+      for (const CmaxPart& p : cm) bits = std::max(bits, p.v[d]);
       double v;
-      std::memcpy(&v, &cm[d], sizeof(double));
+      std::memcpy(&v, &bits, sizeof(double));
       cmax_out[d] = v;
     }
     if (c->cfg.physics == AMRVAC_GLM) {   // c_h in every direction
@@ -1058,7 +1060,7 @@ static amrvac_status enqueue_steps(amrvac_ctx* c, int scheme, double cfl, const 
     launch_copy_interior(state_table(c), c->d_ptiles, np, V->tx, V->ty, V->tz, c->nvar, 0, 2, grid, c->stream);
   }
   launch_set_control(c->d_ctl, dt_fixed ? *dt_fixed : 0.0, cfl, t_inout ? *t_inout : 0.0, c->stream);
-  if (nsteps > 0) launch_cmax_of(c, 0, 0, c->stream);
+  if (nsteps > 0) launch_cmax_of(c, 0, 0, c->stream, true);
   const int exec = c->exec;
   if (use_graph && exec == AMRVAC_EXEC_BATCHED && nsteps > 0) {
     // both graphs are captured on first use, so a later longer call does

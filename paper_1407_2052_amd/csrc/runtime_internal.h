@@ -131,7 +131,8 @@ struct EmitPlan {
 };
 void enqueue_step_outs(amrvac_ctx* c, int scheme, int exec, hipStream_t s, int U, const int* outs, int S,
                        const EmitPlan* emit = nullptr);
-void launch_cmax_of(amrvac_ctx* c, int buf, int slot, hipStream_t s);
+// cleared: slot 0 straight after launch_set_control, which clears it
+void launch_cmax_of(amrvac_ctx* c, int buf, int slot, hipStream_t s, bool cleared = false);
 amrvac_status read_status(amrvac_ctx* c);
 // Shu-Osher table (Sect. 2.3) as used by the stage recipes: alpha[i][k],
 // beta[i][k] for stages i = 1..s.

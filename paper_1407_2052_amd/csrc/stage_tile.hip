@@ -29,6 +29,8 @@
 // on the 256^3 list: fewer halo cells, but nothing runs during its barriers.
 #include "device_math.h"
 
+#include <cstddef>
+
 namespace amrvac {
 
 namespace {
@@ -142,13 +144,9 @@ __global__ void __launch_bounds__(NT, WPE) k_tile(StageParams P) {
   const double gamma = P.gamma;
 
   double cin[3];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) cin[d] = __longlong_as_double((long long)constant_ptr(ctl)->cm[P.cm_in][d]);
+  load_cmax<NDIM>(ctl, P.cm_in, cin);
   const double dt = FORM == RHS ? 0.0 : constant_ptr(ctl)->dt;
-  if (P.cm_reset >= 0 && blockIdx.x == 0 && tid == 0) {
-#pragma unroll
-    for (int d = 0; d < 3; ++d) ctl->cm[P.cm_reset][d] = 0ull;
-  }
+  if (P.cm_reset >= 0 && blockIdx.x == 0) clear_cmax(ctl, P.cm_reset);
   double run[3] = {0.0, 0.0, 0.0};
   bool ok_all = true;
 
@@ -246,12 +244,18 @@ __global__ void __launch_bounds__(NT, WPE) k_tile(StageParams P) {
     const cptr<TileInfo> T = tiles + t;
     const int tend[3] = {T->e[0], T->e[1], T->e[2]};
     // the next tile's table entry on its way into the scalar cache: one word
-    // of each 64-byte line, consumed at the end of this tile
-    int touch[sizeof(TileInfo) / 64];
+    // of each 64-byte line this launch reads (the header's, the halos' and both
+    // own cells'), consumed at the end of this tile
+    constexpr int NTOUCH = 6;
+    int touch[NTOUCH];
     {
+      static_assert(sizeof(TileInfo) == 512 && offsetof(TileInfo, side) == 64, "lines of the tile table");
       const cptr<int> line = (cptr<int>)(t + sched.step < sched.end ? T + sched.step : T);
+      const int first = pad_in ? 4 : 1;
+      touch[0] = line[0];
 #pragma unroll
-      for (int q = 0; q < (int)(sizeof(TileInfo) / 64); ++q) touch[q] = line[16 * q];
+      for (int q = 0; q < 4; ++q) touch[1 + q] = line[16 * (first + q)];
+      touch[5] = line[16 * (pad_in ? 4 : 7)];
     }
     auto inside = [&](const int* a) { return a[0] < tend[0] && a[1] < tend[1] && a[2] < tend[2]; };
     if constexpr (OWNER) {
@@ -506,7 +510,7 @@ __global__ void __launch_bounds__(NT, WPE) k_tile(StageParams P) {
       }
     }
 #pragma unroll
-    for (int q = 0; q < (int)(sizeof(TileInfo) / 64); ++q) asm volatile("" ::"s"(touch[q]));
+    for (int q = 0; q < NTOUCH; ++q) asm volatile("" ::"s"(touch[q]));
   }
   };
   if (owner) tile_loop(std::true_type{});
@@ -524,7 +528,7 @@ __global__ void __launch_bounds__(NT, WPE) k_tile(StageParams P) {
       for (int d = 0; d < NDIM; ++d) {
         double m = red[0][d];
         for (int q = 1; q < TC / 64; ++q) m = fmax(m, red[q][d]);
-        atomicMax(&ctl->cm[P.cm_out][d], (unsigned long long)__double_as_longlong(m));
+        fold_cmax(ctl, P.cm_out, d, m);
       }
     }
   }
