@@ -94,6 +94,9 @@ typedef enum { AMRVAC_RK3 = 0, AMRVAC_SSPRK43 = 1, AMRVAC_SSPRK54 = 2 } amrvac_s
  *  BATCHED_SINGLE:  one persistent fused launch per stage over the whole
  *                   list (each XCD's share holds an eighth of every class),
  *                   steps replayed from HIP graphs as for BATCHED.
+ * In either batched form a small 1D list (hydro or ideal MHD, at most 1024 or
+ * 640 cells with the ghost cells of fixed faces) runs whole steps in one
+ * launch of one work-group.
  * Setting a batched form rebuilds the work list; the autotuner times tile
  * shapes in the form that is set. */
 typedef enum { AMRVAC_EXEC_PER_BLOCK = 0, AMRVAC_EXEC_BATCHED = 1, AMRVAC_EXEC_BATCHED_SINGLE = 2 } amrvac_exec;

@@ -184,6 +184,54 @@ struct CmaxParams {
   double eta_h;         // Hall MHD: the whistler speed enters c_max
 };
 
+// ---------------------------------------------------------------------------
+// Runs of steps of a small 1D list in one launch (line.hip).
+// ---------------------------------------------------------------------------
+// Threads of the one work-group: hydro 16 wavefronts; MHD 10, whose three
+// states of 8 variables need more registers than 16 wavefronts leave a thread.
+constexpr int line_threads(bool mhd) { return mhd ? 640 : 1024; }
+// Doubles per line entry in LDS.
+constexpr int line_stride(int nvar) { return 2 * nvar + 1; }
+// Interfaces per reconstruction item that the kernel is compiled for.
+constexpr int LINE_RUNS[] = {4, 5, 7, 9, 13};
+constexpr int LINE_LDS_BYTES = 160 * 1024;
+constexpr int LINE_STEPS = 64;                // steps per launch
+
+// A cell of the list (then the ghost cells of its fixed faces), one per
+// thread: where its state is, its entry in the lines of split fluxes and up to
+// two halo entries that repeat it, its lower interface, 0.5 / dx.
+struct LineCell {
+  double* u;
+  long long vs;
+  double hidx;
+  int pos, dup[2], ifc;
+};
+
+// Consecutive interfaces of a block, the first above line entry pos + 2; kr: LIM03's scale for doubled data.
+struct LineRun {
+  int pos, ifc;
+  double kr;
+};
+
+// One stage's update: dst = a0 X + a1 u + dt b L (x: 0 no X, 1 the step's
+// initial state, 2 the accumulator) and, with y != 0, the accumulator
+// S = sa0 Y + sa1 u + dt sb L.
+struct LineStage {
+  int x, y;
+  double a0, a1, b, sa0, sa1, sb;
+};
+
+struct LineParams {
+  const LineCell* cells;
+  const LineRun* runs;
+  Control* ctl;
+  double gamma, dt_fixed, cfl, t0, dx_min;
+  int ncells, nghost, nruns, length, nifc;
+  int run;                      // interfaces per item
+  int nsteps, nstages, first;   // first: the start time is t0, else ctl->t
+  LineStage stage[5];
+};
+
 // One fixed face of a block list (the adjoint's boundary-data pass).
 struct FixedFace {
   int block;

@@ -97,6 +97,10 @@ static void free_tables(amrvac_ctx* c) {
   c->d_dxtab = nullptr;
   c->d_rhs_ptrs = nullptr;
   c->nslots = 0;
+  if (c->d_line_cells) (void)hipFree(c->d_line_cells);
+  if (c->d_line_runs) (void)hipFree(c->d_line_runs);
+  c->d_line_cells = nullptr;
+  c->d_line_runs = nullptr;
 }
 
 // ---------------------------------------------------------------------------
@@ -685,6 +689,96 @@ static bool blocks_ok(int nd, const amrvac_block* blocks, int nblocks, std::stri
   return true;
 }
 
+// Builds the tables of the one-launch form for a small 1D list, or leaves them
+// null.  The form needs a thread per cell and per fixed ghost cell and the
+// split and interface fluxes in one CU's LDS.
+static size_t line_lds(const amrvac_ctx* c, int length, int nifc) {
+  return 8ull * ((unsigned long long)line_stride(c->nvar) * (length + nifc) + line_threads(c->cfg.physics == AMRVAC_MHD) / 64);
+}
+
+static amrvac_status build_line(amrvac_ctx* c) {
+  c->hline_cells.clear();
+  c->hline_runs.clear();
+  if (c->cfg.ndim != 1 || c->cfg.physics == AMRVAC_GLM || c->cfg.eta_h > 0.0) return AMRVAC_OK;
+  const bool mhd = c->cfg.physics == AMRVAC_MHD, lim = c->cfg.recon == AMRVAC_LIM03;
+  const int threads = line_threads(mhd);
+  if (c->total_cells > threads) return AMRVAC_OK;
+  const int nb = (int)c->hb.size();
+  std::vector<int> base(nb), ibase(nb);   // of each block's line (n + 6 entries) and interfaces (n + 1)
+  int length = 0, nifc = 0, nghost = 0, shortest = threads;
+  for (int b = 0; b < nb; ++b) {
+    const int n = c->hb[b].n[0];
+    base[b] = length;
+    ibase[b] = nifc;
+    length += n + 2 * NG;
+    nifc += n + 1;
+    shortest = std::min(shortest, n + 1);
+    for (int f = 0; f < 2; ++f) nghost += c->hb[b].nbr[f] < 0 ? NG : 0;
+  }
+  if (c->total_cells + nghost > threads || line_lds(c, length, nifc) > (size_t)LINE_LDS_BYTES) return AMRVAC_OK;
+  // the run length whose slowest thread does least, a run of r interfaces
+  // counted as r + 2 (what neighbouring runs repeat); no longer than the
+  // shortest block's interfaces (n >= 3: at least 4)
+  long long cost = -1;
+  for (int run : LINE_RUNS) {
+    if (run > shortest || (run % 2 == 0 && shortest > run)) continue;   // odd lengths where there is a choice (LDS banks)
+    long long items = 0;
+    for (int b = 0; b < nb; ++b) items += 2ll * c->nvar * ((c->hb[b].n[0] + run) / run);
+    const long long k = (items + threads - 1) / threads * (run + 2);
+    if (cost < 0 || k < cost) {
+      cost = k;
+      c->line_run = run;
+    }
+  }
+  const int RUN = c->line_run;
+  c->line_dx_min = c->hdev[0].dx[0];
+  std::vector<LineCell> ghosts;
+  for (int b = 0; b < nb; ++b) {
+    const BlockDev& D = c->hdev[b];
+    const int n = D.n[0];
+    c->line_dx_min = std::min(c->line_dx_min, D.dx[0]);
+    for (int i = -NG; i < n + NG; ++i) {
+      const bool lo = i < 0, hi = i >= n;
+      if ((lo && D.nbr[0] >= 0) || (hi && D.nbr[1] >= 0)) continue;   // a neighbour's cell
+      LineCell k{};
+      k.u = D.u + (i + NG);
+      k.vs = D.P[0];
+      k.hidx = 0.5 * D.inv_dx[0];
+      k.pos = base[b] + NG + i;
+      k.ifc = ibase[b] + i;
+      k.dup[0] = k.dup[1] = -1;
+      if (!lo && !hi) {
+        // in the upper halo of the neighbour below, the lower halo of the one above
+        if (i < NG && D.nbr[0] >= 0) k.dup[0] = base[D.nbr[0]] + NG + c->hb[D.nbr[0]].n[0] + i;
+        if (i >= n - NG && D.nbr[1] >= 0) k.dup[1] = base[D.nbr[1]] + (i - n + NG);
+        c->hline_cells.push_back(k);
+      } else {
+        ghosts.push_back(k);
+      }
+    }
+    // runs of the block's n + 1 interfaces; the last one ends at the last
+    // interface
+    const double kr1 = (0.5 * D.inv_dx[0]) * (0.5 * D.inv_dx[0]);
+    for (int q = 0; q < n + 1; q += RUN) {
+      const int k0 = std::min(q, n + 1 - RUN);
+      c->hline_runs.push_back(LineRun{base[b] + k0, ibase[b] + k0, kr1});
+    }
+  }
+  c->line_ncells = (int)c->hline_cells.size();
+  c->hline_cells.insert(c->hline_cells.end(), ghosts.begin(), ghosts.end());
+  c->line_length = length;
+  c->line_nifc = nifc;
+  c->line_lds = line_lds(c, length, nifc);
+  HIP_TRY(c, prepare_line(mhd, lim, RUN));
+  HIP_TRY(c, hipMalloc(&c->d_line_cells, sizeof(LineCell) * c->hline_cells.size()));
+  HIP_TRY(c, hipMalloc(&c->d_line_runs, sizeof(LineRun) * c->hline_runs.size()));
+  HIP_TRY(c, hipMemcpyAsync(c->d_line_cells, c->hline_cells.data(), sizeof(LineCell) * c->hline_cells.size(),
+                            hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(c->d_line_runs, c->hline_runs.data(), sizeof(LineRun) * c->hline_runs.size(),
+                            hipMemcpyHostToDevice, c->stream));
+  return AMRVAC_OK;
+}
+
 extern "C" {
 
 int amrvac_abi_version(void) { return AMRVAC_ABI_VERSION; }
@@ -823,7 +917,8 @@ amrvac_status amrvac_set_blocks(amrvac_ctx* c, const amrvac_block* blocks, int n
   HIP_TRY(c, hipMemcpyAsync(c->d_dxtab, dxt.data(), sizeof(double) * dxt.size(), hipMemcpyHostToDevice,
                             c->stream));
   HIP_TRY(c, hipMalloc(&c->d_rhs_ptrs, sizeof(double*) * nblocks));
-  amrvac_status st = build_tiles(c);
+  amrvac_status st = build_line(c);
+  if (st == AMRVAC_OK) st = build_tiles(c);
   if (st != AMRVAC_OK) return st;
   // control: ndx
   Control h{};
@@ -1037,6 +1132,50 @@ static amrvac_status check_step_args(amrvac_ctx* c, int scheme, double cfl, cons
   return AMRVAC_OK;
 }
 
+// The steps of a small 1D list, LINE_STEPS per launch.
+static amrvac_status line_steps(amrvac_ctx* c, int scheme, double cfl, const double* dt_fixed, int nsteps,
+                                double t0) {
+  LineParams p{};
+  p.cells = c->d_line_cells;
+  p.runs = c->d_line_runs;
+  p.ctl = c->d_ctl;
+  p.gamma = c->cfg.gamma;
+  p.dt_fixed = dt_fixed ? *dt_fixed : 0.0;
+  p.cfl = cfl;
+  p.t0 = t0;
+  p.dx_min = c->line_dx_min;
+  p.ncells = c->line_ncells;
+  p.nghost = (int)c->hline_cells.size() - c->line_ncells;
+  p.nruns = (int)c->hline_runs.size();
+  p.length = c->line_length;
+  p.nifc = c->line_nifc;
+  p.run = c->line_run;
+  p.nstages = scheme_stages(scheme);
+  // buffer ids as in the stage recipes: 0 the step's state, 3 the accumulator
+  const int outs[6] = {0, 1, 2, 1, 2, 0};
+  int o[6];
+  for (int i = 1; i <= p.nstages; ++i) o[i] = i == p.nstages ? 0 : outs[i];
+  const std::vector<Recipe> r = recipes(scheme, 0, o, 3);
+  for (int i = 0; i < p.nstages; ++i) {
+    LineStage& g = p.stage[i];
+    const Recipe& q = r[i];
+    g.x = q.nsrc == 1 ? 0 : q.src[0] == 3 ? 2 : 1;
+    g.a0 = q.a[0];
+    g.a1 = q.nsrc == 1 ? q.a[0] : q.a[1];
+    g.b = q.b;
+    g.y = q.sdst < 0 ? 0 : q.ssrc[0] == 3 ? 2 : 1;
+    g.sa0 = q.sa[0];
+    g.sa1 = q.sa[1];
+    g.sb = q.sb;
+  }
+  for (int done = 0; done < nsteps; done += LINE_STEPS) {
+    p.first = done == 0 ? 1 : 0;
+    p.nsteps = std::min(LINE_STEPS, nsteps - done);
+    HIP_TRY(c, launch_line(c->cfg.physics == AMRVAC_MHD, c->cfg.recon == AMRVAC_LIM03, p, c->line_lds, c->stream));
+  }
+  return AMRVAC_OK;
+}
+
 // Steps per graph of the multi-step graph: a graph launch costs about 6 us
 // on top of its kernels (2D Euler 256^2: 81 us per step replaying a one-step
 // graph, 75 us launching the kernels one by one, 74 us replaying 8-step
@@ -1050,6 +1189,8 @@ constexpr int GRAPH_MULTI_KEY = 16;   // graphs[scheme + GRAPH_MULTI_KEY]: the m
 // form replays cached graphs of GRAPH_STEPS steps and of one step.
 static amrvac_status enqueue_steps(amrvac_ctx* c, int scheme, double cfl, const double* dt_fixed, int nsteps,
                                    double* t_inout, bool use_graph) {
+  if (c->d_line_cells && c->exec == AMRVAC_EXEC_BATCHED && c->hptiles.empty() && nsteps > 0)
+    return line_steps(c, scheme, cfl, dt_fixed, nsteps, t_inout ? *t_inout : 0.0);
   if (!c->hptiles.empty() && nsteps > 0) {
     // passive blocks: their current state in the stage buffers A and B,
     // which active neighbours read as halo at every stage

@@ -25,6 +25,9 @@ void launch_set_control(Control* ctl, double dt_fixed, double cfl, double t, hip
 void launch_copy_interior(const StateTable& st, const Tile* tiles, int ntiles, int tx, int ty, int tz, int nv,
                           int src, int dst, int grid, hipStream_t s);
 
+hipError_t launch_line(bool mhd, bool lim, const LineParams& p, size_t lds, hipStream_t s);
+hipError_t prepare_line(bool mhd, bool lim, int run);
+
 // A range of the tile list that one batched stage launch covers.
 struct LaunchGroup {
   int tile_begin, ntiles, grid;
@@ -107,6 +110,15 @@ struct amrvac_ctx {
   int divb_cap = 0;
 
   std::map<int, GraphEntry> graphs;
+
+  // small 1D lists: the tables of line.hip (null where the list does not fit)
+  amrvac::LineCell* d_line_cells = nullptr;
+  amrvac::LineRun* d_line_runs = nullptr;
+  std::vector<amrvac::LineCell> hline_cells;
+  std::vector<amrvac::LineRun> hline_runs;
+  int line_ncells = 0, line_length = 0, line_nifc = 0, line_run = 0;
+  double line_dx_min = 0.0;
+  size_t line_lds = 0;
 };
 
 
