@@ -89,8 +89,9 @@ typedef enum { AMRVAC_RK3 = 0, AMRVAC_SSPRK43 = 1, AMRVAC_SSPRK54 = 2 } amrvac_s
  *  BATCHED:         persistent fused launches over the block list, one per
  *                   block-size class (blocks of equal cell count; a class
  *                   with fewer tiles than twice the resident work-groups
- *                   joins the next), steps replayed from HIP graphs (of 8
- *                   steps, and of one step for the remainder of a call);
+ *                   joins the next), runs of 8 steps replayed from a HIP
+ *                   graph (captured by the first call that long), the
+ *                   remainder of a call launched kernel by kernel;
  *  BATCHED_SINGLE:  one persistent fused launch per stage over the whole
  *                   list (each XCD's share holds an eighth of every class),
  *                   steps replayed from HIP graphs as for BATCHED.

@@ -31,6 +31,7 @@ struct Adj {
   const VjpVariant* V;
   std::vector<Tile> htiles;           // tiles of the recompute's shape
   Tile* d_tiles = nullptr;
+  TileInfo* d_info = nullptr;         // of the recompute's tiles, for a role-split kernel
   std::vector<Tile> hvtiles;          // tiles of the VJP's shape
   Tile* d_vtiles = nullptr;
   double* d_hist = nullptr;   // c_max of every stage state of a segment, 3 per state
@@ -52,6 +53,7 @@ struct Adj {
   ~Adj() {
     if (side) (void)hipStreamSynchronize(side);
     if (d_tiles) (void)hipFree(d_tiles);
+    if (d_info) (void)hipFree(d_info);
     if (d_vtiles) (void)hipFree(d_vtiles);
     if (d_hist) (void)hipFree(d_hist);
     if (d_cpart) (void)hipFree(d_cpart);
@@ -168,7 +170,9 @@ extern "C" amrvac_status amrvac_ssprk_adjoint(amrvac_ctx* c, int scheme, double 
   const int k = std::max(1, std::min(ckpt_every, std::max(N, 1)));
   const int M = (N + k - 1) / k;   // segments
   const VjpVariant* VV = vjp_variant(c->cfg.ndim, c->cfg.physics == AMRVAC_MHD);
-  const StageVariant* EV = emit_variant(c->cfg.ndim, c->cfg.physics == AMRVAC_MHD, c->cfg.recon);
+  const bool mhd = c->cfg.physics == AMRVAC_MHD;
+  const StageVariant* EV = offsets_fit(c) ? tile_emit_variant(c->cfg.ndim, mhd, c->cfg.recon) : nullptr;
+  if (!EV) EV = emit_variant(c->cfg.ndim, mhd, c->cfg.recon);
   if (!VV || !EV) return ctx_fail(c, AMRVAC_ERR_UNSUPPORTED, "ssprk_adjoint: no kernel for this ndim/physics");
   // Lists whose recompute and VJP launches hold at most two work-groups per
   // CU leave most of the GPU idle in each launch: there the next segment is
@@ -292,6 +296,10 @@ extern "C" amrvac_status amrvac_ssprk_adjoint(amrvac_ctx* c, int scheme, double 
   if ((st = hip_ok(hipMemcpyAsync(adj.d_tiles, adj.htiles.data(), sizeof(Tile) * nt, hipMemcpyHostToDevice,
                                   c->stream), "upload")) != AMRVAC_OK)
     return st;
+  if (EV->info > 0) {
+    if ((st = hip_ok(hipMalloc(&adj.d_info, sizeof(TileInfo) * nt), "hipMalloc")) != AMRVAC_OK) return st;
+    launch_tile_info(c->d_blocks, adj.d_tiles, adj.d_info, nt, c->cfg.ndim, EV->info, EV->tx, EV->ty, EV->tz, c->stream);
+  }
   if ((st = hip_ok(hipMemcpyAsync(adj.d_vtiles, adj.hvtiles.data(), sizeof(Tile) * nvt, hipMemcpyHostToDevice,
                                   c->stream), "upload")) != AMRVAC_OK)
     return st;
@@ -373,6 +381,7 @@ extern "C" amrvac_status amrvac_ssprk_adjoint(amrvac_ctx* c, int scheme, double 
       EmitPlan plan{};
       plan.var = EV;
       plan.tiles = adj.d_tiles;
+      plan.info = adj.d_info;
       plan.ntiles = nt;
       plan.grid = adj.grid_emit;
       for (int i = 0; i < s; ++i) {

@@ -169,6 +169,7 @@ struct StageVariant {
 };
 
 const StageVariant* tile_variants(int* count);   // stage_tile.hip
+const StageVariant* tile_emit_variant(int ndim, int mhd, int rec);   // stage_emit.hip, or nullptr
 void launch_tile_info(const BlockDev* blocks, const Tile* tiles, TileInfo* info, int ntiles, int ndim, int hg, int tx,
                       int ty, int tz, hipStream_t s);
 

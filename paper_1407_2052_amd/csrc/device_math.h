@@ -435,8 +435,10 @@ __device__ __forceinline__ void mp5_run(const double* f, double* out, int* code)
 // The values of mp5_run<RUN, false>, one interface after the other with only
 // what the next one needs held: for kernels whose registers are few.  The
 // barriers keep the scheduler from opening several interfaces at once.
+// Returns a bit per interface: its value was clamped (its piece is not fL).
 template <int RUN>
-__device__ __forceinline__ void mp5_stream(const double* f, double* out) {
+__device__ __forceinline__ unsigned mp5_stream(const double* f, double* out) {
+  unsigned clamped = 0;
   double D[4];   // differences of the interface's stencil
   D[0] = f[1] - f[0];
   D[1] = f[2] - f[1];
@@ -451,7 +453,10 @@ __device__ __forceinline__ void mp5_stream(const double* f, double* out) {
     const double m4p = m4pair(dc, dcp);
     const double dn = fmin(D[2], 0.0), dp = fmax(D[2], 0.0), h = 0.5 * D[2];
     Mp5Bounds q;
-    out[kk] = f[kk + 2] + mp5_clamp(mp5_fifth(D), dn, dp, h, dn1, dp1, h1, m4p, m4m, q);
+    const double g = mp5_fifth(D);
+    const double r = mp5_clamp(g, dn, dp, h, dn1, dp1, h1, m4p, m4m, q);
+    out[kk] = f[kk + 2] + r;
+    clamped |= (r != g ? 1u : 0u) << kk;
     D[0] = D[1];
     D[1] = D[2];
     D[2] = D[3];
@@ -462,6 +467,22 @@ __device__ __forceinline__ void mp5_stream(const double* f, double* out) {
     h1 = h;
     __builtin_amdgcn_sched_barrier(0);
   }
+  return clamped;
+}
+
+// The piece of one reconstruction from its stencil, as mp5_run<1, true> finds
+// it.
+__device__ __forceinline__ int mp5_code(double a, double b, double c, double d, double e) {
+  const double D[4] = {b - a, c - b, d - c, e - d};
+  const double dm = D[1] - D[0], d0 = D[2] - D[1], dp = D[3] - D[2];
+  const double m4m = m4pair(dm, d0), m4p = m4pair(d0, dp);
+  const int kp = m4p == 0.0 ? 0 : fma(4.0, d0, -dp) == m4p ? 1 : fma(4.0, dp, -d0) == m4p ? 2 : d0 == m4p ? 3 : 4;
+  const int km = m4m == 0.0 ? 0 : fma(4.0, d0, -dm) == m4m ? 1 : fma(4.0, dm, -d0) == m4m ? 2 : d0 == m4m ? 3 : 4;
+  const double g = mp5_fifth(D);
+  Mp5Bounds q;
+  (void)mp5_clamp(g, fmin(D[2], 0.0), fmax(D[2], 0.0), 0.5 * D[2], fmin(D[1], 0.0), fmax(D[1], 0.0), 0.5 * D[1], m4p,
+                  m4m, q);
+  return mp5_piece(g, D[2], D[1], q, kp, km);
 }
 
 __device__ __forceinline__ double mp5(double a, double b, double c, double d, double e) {

@@ -147,7 +147,7 @@ static const StageVariant* pick_variant(const amrvac_ctx* c, int want) {
 // of the tile's first cell: at most 16 rows and 3 + 3 halo rows, or 4 planes
 // and 3 + 3 halo planes, of a padded block (2^28 cells leave the factor 8 of a
 // double inside 2^31).
-static bool offsets_fit(const amrvac_ctx* c) {
+bool amrvac::offsets_fit(const amrvac_ctx* c) {
   for (const amrvac_block& q : c->hb) {
     const long long s1 = q.n[0] + 2 * NG, s2 = s1 * (q.n[1] + 2 * NG);
     if ((c->cfg.ndim >= 2 ? 24 * s1 : 0) + (c->cfg.ndim >= 3 ? 12 * s2 : 0) > (1ll << 28)) return false;
@@ -589,6 +589,7 @@ void enqueue_step_outs(amrvac_ctx* c, int scheme, int exec, hipStream_t s, int U
     p.decay_psi = (i == ns && c->cfg.physics == AMRVAC_GLM) ? 1 : 0;
     if (emit) {
       p.tiles = emit->tiles;
+      p.info = emit->info;
       p.tile_begin = 0;
       p.ntiles = emit->ntiles;
       p.codes = emit->codes[i - 1];
@@ -1176,17 +1177,18 @@ static amrvac_status line_steps(amrvac_ctx* c, int scheme, double cfl, const dou
   return AMRVAC_OK;
 }
 
-// Steps per graph of the multi-step graph: a graph launch costs about 6 us
-// on top of its kernels (2D Euler 256^2: 81 us per step replaying a one-step
-// graph, 75 us launching the kernels one by one, 74 us replaying 8-step
-// graphs), so runs of steps replay 8-step graphs and the remainder the
-// one-step graph.
+// Steps per graph: a graph launch costs about 6 us on top of its kernels (2D
+// Euler 256^2, before the stages got shorter: 81 us per step replaying a
+// one-step graph, 75 us launching the kernels one by one, 74 us replaying
+// 8-step graphs), so runs of steps replay 8-step graphs and the remainder of a
+// call is launched kernel by kernel.  The graph is captured by the first call
+// of at least GRAPH_STEPS steps: shorter calls never pay for the capture
+// (0.3 to 0.8 ms of the first call on a new context).
 constexpr int GRAPH_STEPS = 8;
-constexpr int GRAPH_MULTI_KEY = 16;   // graphs[scheme + GRAPH_MULTI_KEY]: the multi-step graph
 
 // The steps of amrvac_ssprk_step on the stage buffers the state tables
 // point at (context scratch, or the fixed array); with use_graph the batched
-// form replays cached graphs of GRAPH_STEPS steps and of one step.
+// form replays a cached graph of GRAPH_STEPS steps.
 static amrvac_status enqueue_steps(amrvac_ctx* c, int scheme, double cfl, const double* dt_fixed, int nsteps,
                                    double* t_inout, bool use_graph) {
   if (c->d_line_cells && c->exec == AMRVAC_EXEC_BATCHED && c->hptiles.empty() && nsteps > 0)
@@ -1204,29 +1206,22 @@ static amrvac_status enqueue_steps(amrvac_ctx* c, int scheme, double cfl, const 
   if (nsteps > 0) launch_cmax_of(c, 0, 0, c->stream, true);
   const int exec = c->exec;
   if (use_graph && exec == AMRVAC_EXEC_BATCHED && nsteps > 0) {
-    // both graphs are captured on first use, so a later longer call does
-    // not capture inside its own run
-    auto capture = [&](GraphEntry& g, int steps) -> amrvac_status {
-      HIP_TRY(c, hipStreamBeginCapture(c->cap, hipStreamCaptureModeRelaxed));
-      for (int k = 0; k < steps; ++k) enqueue_step(c, scheme, exec, c->cap, 0, 1, 2, 3, 0);
-      hipError_t e = hipStreamEndCapture(c->cap, &g.graph);
-      if (e != hipSuccess) {
-        g.graph = nullptr;
-        return fail(c, AMRVAC_ERR_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
-      }
-      HIP_TRY(c, hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0));
-      return AMRVAC_OK;
-    };
-    GraphEntry& g1 = c->graphs[scheme];
-    GraphEntry& gm = c->graphs[scheme + GRAPH_MULTI_KEY];
-    if (!g1.exec || !gm.exec) {
-      amrvac_status st = g1.exec ? AMRVAC_OK : capture(g1, 1);
-      if (st == AMRVAC_OK && !gm.exec) st = capture(gm, GRAPH_STEPS);
-      if (st != AMRVAC_OK) return st;
-    }
     int it = 0;
-    for (; it + GRAPH_STEPS <= nsteps; it += GRAPH_STEPS) HIP_TRY(c, hipGraphLaunch(gm.exec, c->stream));
-    for (; it < nsteps; ++it) HIP_TRY(c, hipGraphLaunch(g1.exec, c->stream));
+    if (nsteps >= GRAPH_STEPS) {
+      GraphEntry& g = c->graphs[scheme];
+      if (!g.exec) {
+        HIP_TRY(c, hipStreamBeginCapture(c->cap, hipStreamCaptureModeRelaxed));
+        for (int k = 0; k < GRAPH_STEPS; ++k) enqueue_step(c, scheme, exec, c->cap, 0, 1, 2, 3, 0);
+        hipError_t e = hipStreamEndCapture(c->cap, &g.graph);
+        if (e != hipSuccess) {
+          g.graph = nullptr;
+          return fail(c, AMRVAC_ERR_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
+        }
+        HIP_TRY(c, hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0));
+      }
+      for (; it + GRAPH_STEPS <= nsteps; it += GRAPH_STEPS) HIP_TRY(c, hipGraphLaunch(g.exec, c->stream));
+    }
+    for (; it < nsteps; ++it) enqueue_step(c, scheme, exec, c->stream, 0, 1, 2, 3, 0);
   } else {
     for (int it = 0; it < nsteps; ++it) enqueue_step(c, scheme, exec, c->stream, 0, 1, 2, 3, 0);
   }

@@ -127,6 +127,7 @@ namespace amrvac {
 amrvac_status ctx_fail(amrvac_ctx* c, amrvac_status st, const char* fmt, ...);
 amrvac_status ensure_slots(amrvac_ctx* c, int n);
 StateTable state_table(const amrvac_ctx* c);
+bool offsets_fit(const amrvac_ctx* c);   // the role-split kernels' limit on a block's extents
 int scheme_stages(int scheme);
 // One step of `scheme` with state buffer U (read), per-stage output buffers
 // outs[1..s] (outs[s] receives U^{n+1}) and low-storage accumulator S.
@@ -135,6 +136,7 @@ int scheme_stages(int scheme);
 struct EmitPlan {
   const StageVariant* var;
   const Tile* tiles;
+  const TileInfo* info;   // of the same tiles, for a role-split kernel
   int ntiles;
   int grid;
   unsigned char* codes[6];
