@@ -34,6 +34,7 @@ struct Adj {
   TileInfo* d_info = nullptr;         // of the recompute's tiles, for a role-split kernel
   std::vector<Tile> hvtiles;          // tiles of the VJP's shape
   Tile* d_vtiles = nullptr;
+  VjpInfo* d_vinfo = nullptr;
   double* d_hist = nullptr;   // c_max of every stage state of a segment, 3 per state
   double* d_cpart = nullptr;
   double** d_ptrs = nullptr;
@@ -55,6 +56,7 @@ struct Adj {
     if (d_tiles) (void)hipFree(d_tiles);
     if (d_info) (void)hipFree(d_info);
     if (d_vtiles) (void)hipFree(d_vtiles);
+    if (d_vinfo) (void)hipFree(d_vinfo);
     if (d_hist) (void)hipFree(d_hist);
     if (d_cpart) (void)hipFree(d_cpart);
     if (d_ptrs) (void)hipFree(d_ptrs);
@@ -105,7 +107,7 @@ struct Adj {
     StateTable st = state_table(c);
     VjpParams p{};
     p.st = st;
-    p.tiles = d_vtiles;
+    p.info = d_vinfo;
     p.ntiles = nvtiles();
     p.ctl = c->d_ctl;
     p.gamma = c->cfg.gamma;
@@ -303,6 +305,8 @@ extern "C" amrvac_status amrvac_ssprk_adjoint(amrvac_ctx* c, int scheme, double 
   if ((st = hip_ok(hipMemcpyAsync(adj.d_vtiles, adj.hvtiles.data(), sizeof(Tile) * nvt, hipMemcpyHostToDevice,
                                   c->stream), "upload")) != AMRVAC_OK)
     return st;
+  if ((st = hip_ok(hipMalloc(&adj.d_vinfo, sizeof(VjpInfo) * nvt), "hipMalloc")) != AMRVAC_OK) return st;
+  launch_vjp_info(c->d_blocks, adj.d_vtiles, adj.d_vinfo, nvt, c->cfg.ndim, VV->tx, VV->ty, VV->tz, c->stream);
   std::vector<double*> hptrs(lam, lam + nb);
   if ((st = hip_ok(hipMemcpyAsync(adj.d_ptrs, hptrs.data(), sizeof(double*) * nb, hipMemcpyHostToDevice, c->stream),
                    "upload")) != AMRVAC_OK)

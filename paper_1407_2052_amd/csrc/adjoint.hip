@@ -212,24 +212,71 @@ struct SweepShape {
   }
 };
 
-// Cell (c[0], c[1], c[2]) of block blk where only c[D] may lie outside the
-// block: the face neighbour that holds it, with c[D] moved into it (nullptr
-// for a fixed face, which the adjoint rejects before any launch).
-template <int D>
-__device__ __forceinline__ const BlockDev* resolve_cell(const StateTable& st, int blk, int* c) {
-  const BlockDev* B = &st.blocks[blk];
-  if (c[D] < 0) {
-    const int nb = B->nbr[2 * D];
-    if (nb < 0) return nullptr;
-    B = &st.blocks[nb];
-    c[D] += B->n[D];
-  } else if (c[D] >= B->n[D]) {
-    const int nb = B->nbr[2 * D + 1];
-    if (nb < 0) return nullptr;
-    c[D] -= B->n[D];
-    B = &st.blocks[nb];
+// Fills the VJP's tile table, one thread per tile.
+__global__ void __launch_bounds__(64) k_vjp_info(const BlockDev* blocks, const Tile* tiles, VjpInfo* info, int ntiles,
+                                               int ndim, int tx, int ty, int tz) {
+  const int t = blockIdx.x * 64 + threadIdx.x;
+  if (t >= ntiles) return;
+  const Tile tl = tiles[t];
+  const BlockDev& B = blocks[tl.block];
+  const int T[3] = {tx, ty, tz};
+  VjpInfo I{};
+  I.block = tl.block;
+  I.org = ((long long)tl.o[2] * B.n[1] + tl.o[1]) * B.n[0] + tl.o[0];
+  I.n0 = B.n[0];
+  I.n1 = B.n[1];
+  I.p1 = B.P[0];
+  I.p2 = B.P[0] * B.P[1];
+  I.pvs = (long long)B.P[0] * B.P[1] * B.P[2];
+  I.u = B.u + (((long long)(tl.o[2] + B.g[2]) * B.P[1] + (tl.o[1] + B.g[1])) * B.P[0] + (tl.o[0] + B.g[0]));
+  for (int d = 0; d < 3; ++d) {
+    const int rem = B.n[d] - tl.o[d];
+    I.e[d] = rem < T[d] ? rem : T[d];
+    I.idx[d] = B.inv_dx[d];
+    const int below = B.n[d] - (tl.o[d] + I.e[d]);
+    I.rem[d] = below < 3 ? below : 3;
+    const long long tr = d == 0 ? (long long)tl.o[1] + (long long)B.n[1] * tl.o[2]
+                       : d == 1 ? (long long)tl.o[0] + (long long)B.n[0] * tl.o[2]
+                                : (long long)tl.o[0] + (long long)B.n[0] * tl.o[1];
+    I.face[d] = B.fco[d] >= 0 ? B.fco[d] + tr : -1;
   }
-  return B;
+  auto set = [&](VjpSide& s, const BlockDev& b, const int* c) {
+    const long long cell = ((long long)c[2] * b.n[1] + c[1]) * b.n[0] + c[0];
+    s.s1 = b.n[0];
+    s.s2 = b.n[0] * b.n[1];
+    s.vs = b.cells;
+    s.slot = b.off + cell;
+    s.code = b.coff + cell;
+    s.fixed = 0;
+  };
+  const int o[3] = {tl.o[0], tl.o[1], tl.o[2]};
+  set(I.side[6], B, o);
+  for (int f = 0; f < 6; ++f) {
+    const int d = f / 2;
+    VjpSide& s = I.side[f];
+    s = I.side[6];
+    s.fixed = 1;
+    if (d >= ndim) continue;
+    int c[3] = {o[0], o[1], o[2]};
+    if (f % 2 == 0) {
+      c[d] -= 3;
+      if (o[d] > 0) {
+        set(s, B, c);
+      } else if (B.nbr[f] >= 0) {
+        c[d] += blocks[B.nbr[f]].n[d];
+        set(s, blocks[B.nbr[f]], c);
+      }
+    } else {
+      c[d] += I.e[d];
+      if (I.rem[d] == 3) {
+        set(s, B, c);
+      } else if (B.nbr[f] >= 0) {
+        c[d] -= B.n[d];
+        set(s, blocks[B.nbr[f]], c);
+      }
+    }
+  }
+  info[t] = I;
 }
 
 // Per tile and direction D:
@@ -244,13 +291,24 @@ __device__ __forceinline__ const BlockDev* resolve_cell(const StateTable& st, in
 //      interface order);
 //   C) per owned cell: split adjoint and flux transpose.
 // Then dst = sum_q lam_a[q] lam_q + scale * nu for the owned cells.
-template <int NDIM, bool MHD, int TX, int TY, int TZ, int NT>
-__global__ void __launch_bounds__(NT) k_vjp(VjpParams P) {
+//
+// What bounds it: latency.  The vector units were busy 22 % of the cycles and
+// wavefronts waited 68 % of theirs, 24 us per 8x8x8 tile of which the
+// instructions take 5: every term of mu and lambda was waited for before the
+// next was asked for, behind a chain of neighbour lookups per direction.  Now
+// the addresses come from a per-tile table by scalar loads, all loads of a
+// direction's halo rows, of its codes and of a lambda term or two are issued before
+// the sweep of the direction before, and the speeds are compared with c_max
+// only where a bound without square roots cannot exclude it.
+template <int NDIM, bool MHD, int TX, int TY, int TZ, int NT, int NMU>
+__global__ void __launch_bounds__(NT, 2) k_vjp(VjpParams P) {
   using E = Eq<NDIM, MHD>;
   using S = SweepShape<TX, TY, TZ>;
   constexpr int NV = E::NV;
   constexpr int TC = S::TC;
-  constexpr int CPT = (TC + NT - 1) / NT;
+  static_assert(TC == NT, "one owned cell per thread");
+  // lambda terms in flight during a sweep, as registers allow
+  constexpr int LPF = NDIM == 3 ? 1 : 2;
   constexpr int MB = cmax_i<cmax_i<NV * S::MROWS(0) * S::PSTR(0), NDIM >= 2 ? NV * S::MROWS(1) * S::PSTR(1) : 0>::v,
                             NDIM >= 3 ? NV * S::MROWS(2) * S::PSTR(2) : 0>::v;
   constexpr int OB = cmax_i<cmax_i<2 * NV * S::T(0) * S::PSTR(0), NDIM >= 2 ? 2 * NV * S::T(1) * S::PSTR(1) : 0>::v,
@@ -284,189 +342,221 @@ __global__ void __launch_bounds__(NT) k_vjp(VjpParams P) {
 #pragma unroll
   for (int q = 0; q < 5; ++q) wc[q] = sW[pc * 5 + q];
 
+  const cptr<VjpInfo> table = constant_ptr(P.info);
+  const int a0 = tid % TX, a1 = (tid / TX) % TY, a2 = tid / (TX * TY);
+  auto slot = [&](int buf) { return (gptr)st.scr + (long long)(buf - 1) * st.slot_stride; };
+
+  // Positions of the halo rows and code words a thread moves for direction D
+  // (item e): row and pencil, and whether the tile has it.
+  auto box_pos = [&](auto Dc, auto Rc, int e, const int* tend, int* a) {
+    constexpr int D = decltype(Dc)::value, R = decltype(Rc)::value;   // R rows along D
+    constexpr int H0 = D == 0 ? R : TX, H1 = D == 1 ? R : TY, H2 = D == 2 ? R : TZ;
+    a[0] = e % H0;
+    a[1] = (e / H0) % H1;
+    a[2] = e / (H0 * H1);
+    bool in = e < H0 * H1 * H2;
+#pragma unroll
+    for (int d = 0; d < 3; ++d)
+      if (d != D) in = in && a[d] < tend[d];
+    return in;
+  };
+  constexpr int HMAX = cmax_i<cmax_i<(6 * TY * TZ + NT - 1) / NT, NDIM >= 2 ? (6 * TX * TZ + NT - 1) / NT : 0>::v,
+                              NDIM >= 3 ? (6 * TX * TY + NT - 1) / NT : 0>::v;
+  constexpr int CMAX = cmax_i<cmax_i<((TX + 5) * TY * TZ + NT - 1) / NT, NDIM >= 2 ? ((TY + 5) * TX * TZ + NT - 1) / NT : 0>::v,
+                              NDIM >= 3 ? ((TZ + 5) * TX * TY + NT - 1) / NT : 0>::v;
+  double hm[HMAX][NMU][NV];          // halo rows of the terms of mu
+  unsigned long long cw[CMAX];       // code words
+  auto load_dir = [&](auto Dc, cptr<VjpInfo> T) {
+    constexpr int D = decltype(Dc)::value;
+    constexpr int NP = S::NP(D), NHB = 6 * NP, NCB = (S::T(D) + 5) * NP;
+    const int tend[3] = {T->e[0], T->e[1], T->e[2]};
+    const int rem = T->rem[D];
+    const cptr<VjpSide> lo = &T->side[2 * D], hi = &T->side[2 * D + 1], own = &T->side[6];
+    // entries by scalar loads, selected per lane
+    const long long ls = held(lo->slot), hs = held(hi->slot), os = held(own->slot);
+    const long long lv = held(lo->vs), hv = held(hi->vs), ov = held(own->vs);
+    const long long lc = held(lo->code), hc = held(hi->code), oc = held(own->code);
+    const int l1 = held(lo->s1), l2 = held(lo->s2), h1 = held(hi->s1), h2 = held(hi->s2);
+    const int o1 = held(own->s1), o2 = held(own->s2);
+    const bool lfix = lo->fixed != 0, hfix = hi->fixed != 0;
+#pragma unroll
+    for (int r = 0; r < (NHB + NT - 1) / NT; ++r) {
+      int a[3];
+      const int e = fresh(tid) + r * NT;
+      box_pos(Dc, std::integral_constant<int, 6>{}, e < NHB ? e : NHB - 1, tend, a);
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+        if (d != D) a[d] = a[d] < tend[d] ? a[d] : tend[d] - 1;
+      const bool up = a[D] >= 3;
+      if (up) a[D] -= 3;
+      // rows of a fixed face hold no mu: any own cell stands in, zeroed later
+      const bool mine = up ? a[D] < rem || hfix : lfix;
+      long long p = up ? hs : ls, vs = up ? hv : lv;
+      int s1 = up ? h1 : l1, s2 = up ? h2 : l2;
+      if (mine) {
+        p = os;
+        vs = ov;
+        s1 = o1;
+        s2 = o2;
+        a[D] = up && a[D] < rem ? a[D] + tend[D] : 0;
+      }
+      p += a[0] + a[1] * s1 + a[2] * s2;
+#pragma unroll
+      for (int q = 0; q < NMU; ++q) {
+        gptr g = slot(P.mu_src[q]) + p;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          hm[r][q][v] = *g;
+          g += vs;
+        }
+      }
+    }
+    using cptr_w = __attribute__((address_space(1))) const unsigned long long*;
+    const cptr_w words = (cptr_w)(P.codes + D * P.code_plane);
+    const long long face = T->face[D];
+#pragma unroll
+    for (int r = 0; r < (NCB + NT - 1) / NT; ++r) {
+      int a[3];
+      const int e = fresh(tid) + r * NT;
+      const bool in = box_pos(Dc, std::integral_constant<int, S::T(D) + 5>{}, e, tend, a);
+      const int x = a[D] - 2;   // tile coordinate of the cell whose lower face it is
+      const bool below = x < 0, above = x >= tend[D] + rem;
+      long long at = -1;
+      if (below) {
+        a[D] = x + 3;
+        if (!lfix) at = lc + (a[0] + a[1] * l1 + a[2] * l2);
+      } else if (!above) {
+        a[D] = x;
+        at = oc + (a[0] + a[1] * o1 + a[2] * o2);
+      } else if (!hfix) {
+        a[D] = x - tend[D];
+        at = hc + (a[0] + a[1] * h1 + a[2] * h2);
+      } else if (x == tend[D] + rem && face >= 0) {
+        const long long tr = D == 0 ? (long long)a[1] + (long long)T->n1 * a[2]
+                           : D == 1 ? (long long)a[0] + (long long)T->n0 * a[2]
+                                    : (long long)a[0] + (long long)T->n0 * a[1];
+        at = P.code_faces + face + tr;
+      }
+      cw[r] = in && at >= 0 && x < tend[D] + 3 ? words[at] : 0ull;
+    }
+  };
+  // the own cell's values of a scratch buffer
+  auto load_own = [&](cptr<VjpInfo> T, int buf, double* u) {
+    const cptr<VjpSide> own = &T->side[6];
+    const int b0 = a0 < T->e[0] ? a0 : T->e[0] - 1, b1 = a1 < T->e[1] ? a1 : T->e[1] - 1;
+    const int b2 = a2 < T->e[2] ? a2 : T->e[2] - 1;
+    gptr p = slot(buf) + (own->slot + (b0 + b1 * own->s1 + b2 * own->s2));
+    const long long vs = own->vs;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) u[v] = p[v * vs];
+  };
+
   // c_max adjoint sums of this work-group's tiles (taken in the fixed tile
   // order of the schedule, then a fixed butterfly: deterministic)
   double cp[3] = {0.0, 0.0, 0.0};
   const TileSchedule sched(P.ntiles);
   for (int t = sched.t; t < sched.end; t += sched.step) {
-    const Tile tl = P.tiles[t];
-    const BlockDev& B = st.blocks[tl.block];
-    int tend[3];
+    const cptr<VjpInfo> T = table + t;
+    const int tend[3] = {T->e[0], T->e[1], T->e[2]};
+    const bool own = a0 < tend[0] && a1 < tend[1] && a2 < tend[2];
+    // owned cell: state, accumulators, mu (formed once per tile; each
+    // direction then loads only the halo rows of mu), lambda combination
+    double uo[NV], nu[NV], muo[NV], acc[NV];
+    {
+      double m[NMU][NV];
+      if (P.in == 0) {
+        const int b0 = a0 < tend[0] ? a0 : tend[0] - 1, b1 = a1 < tend[1] ? a1 : tend[1] - 1;
+        const int b2 = a2 < tend[2] ? a2 : tend[2] - 1;
+        gptr p = (gptr)T->u + (b0 + b1 * T->p1 + (long long)b2 * T->p2);
+        const long long vs = T->pvs;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const int rem = B.n[d] - tl.o[d];
-      tend[d] = rem < S::T(d) ? rem : S::T(d);
-    }
-    // owned cells: state, primitives, accumulators, mu (formed once per
-    // tile; each direction then loads only the halo rows of mu) and the
-    // lambda combination of the output.  Every load is issued first, term by
-    // term over the thread's cells; primitives and the maximiser test follow.
-    double uo[CPT][NV];
-    PrimD wo[CPT];
-    double nu[CPT][NV];
-    double muo[CPT][NV];
-    double acc[CPT][NV];
-    bool own[CPT];
-    int oc[CPT][3];
+        for (int v = 0; v < NV; ++v) uo[v] = p[v * vs];
+      } else {
+        load_own(T, P.in, uo);
+      }
 #pragma unroll
-    for (int r = 0; r < CPT; ++r) {
-      const int cidx = tid + r * NT;
-      const int a0 = cidx % TX, a1 = (cidx / TX) % TY, a2 = cidx / (TX * TY);
-      own[r] = cidx < TC && a0 < tend[0] && a1 < tend[1] && a2 < tend[2];
-      oc[r][0] = tl.o[0] + a0;
-      oc[r][1] = tl.o[1] + a1;
-      oc[r][2] = tl.o[2] + a2;
+      for (int q = 0; q < NMU; ++q) load_own(T, P.mu_src[q], m[q]);
+      load_dir(std::integral_constant<int, 0>{}, T);
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        nu[r][v] = 0.0;
-        muo[r][v] = 0.0;
-        acc[r][v] = 0.0;
-      }
-      if (own[r]) {
-        long long vs;
-        gptr p = cell_addr(st, B, P.in, oc[r][0], oc[r][1], oc[r][2], vs);
+        nu[v] = 0.0;
+        acc[v] = 0.0;
+        muo[v] = 0.0;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) uo[r][v] = p[v * vs];
-      } else {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) uo[r][v] = (v == 0) ? 1.0 : 0.0;
-        uo[r][E::IE] = 1.0;
+        for (int q = 0; q < NMU; ++q) muo[v] = fma(P.mu_a[q], m[q][v], muo[v]);
       }
     }
-    for (int q = 0; q < P.nmu; ++q) {
+    double ri, pr;
+    {
+      PrimD w;
+      prim<NDIM, MHD>(uo, gamma, w);
+      ri = w.ri;
+      pr = w.p;
+      // the cells that realise c_max (bitwise the speed the recompute folded
+      // into it): the lowest key wins
 #pragma unroll
-      for (int r = 0; r < CPT; ++r) {
-        if (!own[r]) continue;
-        long long vs;
-        gptr p = cell_addr(st, B, P.mu_src[q], oc[r][0], oc[r][1], oc[r][2], vs);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) muo[r][v] = fma(P.mu_a[q], p[v * vs], muo[r][v]);
-      }
-    }
-    for (int q = 0; q < P.nlam; ++q) {
-#pragma unroll
-      for (int r = 0; r < CPT; ++r) {
-        if (!own[r]) continue;
-        long long vs;
-        gptr p = cell_addr(st, B, P.lam_src[q], oc[r][0], oc[r][1], oc[r][2], vs);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) acc[r][v] = fma(P.lam_a[q], p[v * vs], acc[r][v]);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < CPT; ++r) {
-      prim<NDIM, MHD>(uo[r], gamma, wo[r]);
-      if (own[r]) {
-        // the cells that realise c_max (bitwise the speed the recompute
-        // folded into it): the lowest key wins
-        const long long key =
-            ((long long)tl.block << 32) | (((long long)oc[r][2] * B.n[1] + oc[r][1]) * B.n[0] + oc[r][0]);
-#pragma unroll
-        for (int d = 0; d < NDIM; ++d)
-          if (fabs(wo[r].v[d]) + fast_speed<MHD>(wo[r], d, gamma) == cin[d])
-            atomicMin(reinterpret_cast<unsigned long long*>(&P.ctl->arg[d]), (unsigned long long)key);
+      for (int d = 0; d < NDIM; ++d) {
+        const bool maybe = own && speed_may_exceed<MHD>(w, d, gamma, cin[d] * (1.0 - 1e-13));
+        if (__ballot(maybe) != 0 && own && fabs(w.v[d]) + fast_speed<MHD>(w, d, gamma) == cin[d]) {
+          const long long key =
+              ((long long)T->block << 32) | (T->org + ((long long)a2 * T->n1 + a1) * T->n0 + a0);
+          atomicMin(reinterpret_cast<unsigned long long*>(&P.ctl->arg[d]), (unsigned long long)key);
+        }
       }
     }
 
     static_for<0, NDIM>([&](auto Dc) {
       constexpr int D = decltype(Dc)::value;
       constexpr int TD = S::T(D), NP = S::NP(D), PS = S::PSTR(D);
-      constexpr int MR = S::MROWS(D), CR = S::CROWS(D);
+      constexpr int MR = S::MROWS(D);
       constexpr int SEG = S::SEG(D, NV, NT), NSEG = TD / SEG;
-      constexpr int C0 = D == 0 ? CR : TX, C1 = D == 1 ? CR : TY, C2 = D == 2 ? CR : TZ;
+      constexpr int NHB = 6 * NP, NCB = (TD + 5) * NP;
       const double c = cin[D];
-      const double idx_d = B.inv_dx[D];
+      const double idx_d = T->idx[D];
 
       // A) mu on the extended box (owned cells from registers, the 3 + 3
-      // halo rows along D from memory), codes on the interface box.  Every
-      // load of this thread is issued first (codes, then the halo rows' mu,
-      // term by term over all of this thread's halo cells); the owned cells'
-      // mu goes to LDS while they are in flight.
-      constexpr int NCB = C0 * C1 * C2, CPTC = (NCB + NT - 1) / NT;
-      unsigned long long cw[CPTC];
-      int cpos[CPTC];
+      // halo rows along D as loaded), codes on the interface box
+      {
+        const int pen = S::PENC(D, a0, a1, a2);
+        const int row = (D == 0 ? a0 : D == 1 ? a1 : a2) + 3;
+        if (own) {
 #pragma unroll
-      for (int r = 0; r < CPTC; ++r) {
-        const int e = tid + r * NT;
-        const int a[3] = {e % C0, (e / C0) % C1, e / (C0 * C1)};
-        bool valid = e < NCB;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) valid = valid && a[d] < tend[d] + (d == D ? 5 : 0);
-        cw[r] = 0ull;
-        cpos[r] = valid ? a[D] * PS + S::PENC(D, a[0], a[1], a[2]) : -1;
-        if (!valid) continue;
-        int cc[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) cc[d] = tl.o[d] + a[d] - (d == D ? 2 : 0);
-        const int up = cc[D];   // before resolve_cell moves it into a neighbour
-        const BlockDev* Bn = resolve_cell<D>(st, tl.block, cc);
-        if (!Bn && up == B.n[D] && B.fco[D] >= 0) {
-          // the interface on a fixed upper face: its word after the interior cells
-          const long long tr = D == 0 ? (long long)cc[1] + (long long)B.n[1] * cc[2]
-                             : D == 1 ? (long long)cc[0] + (long long)B.n[0] * cc[2]
-                                      : (long long)cc[0] + (long long)B.n[0] * cc[1];
-          cw[r] = *(__attribute__((address_space(1))) const unsigned long long*)(P.codes + D * P.code_plane +
-                                                                                (P.code_faces + B.fco[D] + tr) * 8);
+          for (int v = 0; v < NV; ++v) sMu[(v * MR + row) * PS + pen] = muo[v];
         }
-        if (Bn) {
-          const long long cell = ((long long)cc[2] * Bn->n[1] + cc[1]) * Bn->n[0] + cc[0];
-          cw[r] = *(__attribute__((address_space(1))) const unsigned long long*)(P.codes + D * P.code_plane +
-                                                                                (Bn->coff + cell) * 8);
+        const bool lfix = T->side[2 * D].fixed != 0, hfix = T->side[2 * D + 1].fixed != 0;
+        const int rem = T->rem[D];
+#pragma unroll
+        for (int r = 0; r < (NHB + NT - 1) / NT; ++r) {
+          int a[3];
+          const bool in = box_pos(Dc, std::integral_constant<int, 6>{}, fresh(tid) + r * NT, tend, a);
+          const bool up = a[D] >= 3;
+          const bool zero = up ? hfix && a[D] - 3 >= rem : lfix;
+          if (up) a[D] += tend[D];
+          if (in) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+              double m = 0.0;
+#pragma unroll
+              for (int q = 0; q < NMU; ++q) m = fma(P.mu_a[q], hm[r][q][v], m);
+              sMu[(v * MR + a[D]) * PS + S::PENC(D, a[0], a[1], a[2])] = zero ? 0.0 : m;
+            }
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < (NCB + NT - 1) / NT; ++r) {
+          int a[3];
+          const bool in = box_pos(Dc, std::integral_constant<int, TD + 5>{}, fresh(tid) + r * NT, tend, a);
+          if (in && a[D] < tend[D] + 5) sCode[a[D] * PS + S::PENC(D, a[0], a[1], a[2])] = cw[r];
         }
       }
-      constexpr int H0 = D == 0 ? 6 : TX, H1 = D == 1 ? 6 : TY, H2 = D == 2 ? 6 : TZ;
-      constexpr int NHB = H0 * H1 * H2, HPTM = (NHB + NT - 1) / NT;
-      double hm[HPTM][NV];
-      int hrow[HPTM], hpen[HPTM];
-      const BlockDev* hB[HPTM];
-      int hc[HPTM][3];
-#pragma unroll
-      for (int r = 0; r < HPTM; ++r) {
-        const int e = tid + r * NT;
-        int a[3] = {e % H0, (e / H0) % H1, e / (H0 * H1)};
-        bool valid = e < NHB;
-#pragma unroll
-        for (int d = 0; d < 3; ++d)
-          if (d != D) valid = valid && a[d] < tend[d];
-        if (a[D] >= 3) a[D] += tend[D];   // rows 0..2 below the tile, tend+3 .. tend+5 above
-#pragma unroll
-        for (int d = 0; d < 3; ++d) hc[r][d] = tl.o[d] + a[d] - (d == D ? 3 : 0);
-        hB[r] = valid ? resolve_cell<D>(st, tl.block, hc[r]) : nullptr;
-        hrow[r] = valid ? a[D] : -1;
-        hpen[r] = S::PENC(D, a[0], a[1], a[2]);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) hm[r][v] = 0.0;
-      }
-      for (int q = 0; q < P.nmu; ++q) {
-#pragma unroll
-        for (int r = 0; r < HPTM; ++r) {
-          if (!hB[r]) continue;
-          long long vs;
-          gptr p = cell_addr(st, *hB[r], P.mu_src[q], hc[r][0], hc[r][1], hc[r][2], vs);
-#pragma unroll
-          for (int v = 0; v < NV; ++v) hm[r][v] = fma(P.mu_a[q], p[v * vs], hm[r][v]);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < CPT; ++r) {
-        if (!own[r]) continue;
-        const int cidx = tid + r * NT;
-        int a[3] = {cidx % TX, (cidx / TX) % TY, cidx / (TX * TY)};
-        const int pen = S::PENC(D, a[0], a[1], a[2]);
-        const int row = a[D] + 3;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) sMu[(v * MR + row) * PS + pen] = muo[r][v];
-      }
-#pragma unroll
-      for (int r = 0; r < HPTM; ++r) {
-        if (hrow[r] < 0) continue;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) sMu[(v * MR + hrow[r]) * PS + hpen[r]] = hm[r][v];
-      }
-#pragma unroll
-      for (int r = 0; r < CPTC; ++r)
-        if (cpos[r] >= 0) sCode[cpos[r]] = cw[r];
       __syncthreads();
+      // in flight during the sweep: the next direction's halo rows and codes,
+      // and LPF terms of the lambda combination
+      double l[LPF][NV];
+      if constexpr (D + 1 < NDIM) load_dir(std::integral_constant<int, D + 1>{}, T);
+#pragma unroll
+      for (int q = 0; q < LPF; ++q)
+        if (LPF * D + q < P.nlam) load_own(T, P.lam_src[LPF * D + q], l[q]);
 
       // B) sweeps
       constexpr int NITEM = NP * NV * NSEG;
@@ -549,34 +639,46 @@ __global__ void __launch_bounds__(NT) k_vjp(VjpParams P) {
       }
       __syncthreads();
 
-      // C) split adjoint and flux transpose per owned cell
 #pragma unroll
-      for (int r = 0; r < CPT; ++r) {
-        if (!own[r]) continue;
-        const int cidx = tid + r * NT;
-        const int a[3] = {cidx % TX, (cidx / TX) % TY, cidx / (TX * TY)};
-        const int base = a[D] * PS + S::PENC(D, a[0], a[1], a[2]);
+      for (int q = 0; q < LPF; ++q) {
+        if (LPF * D + q < P.nlam) {
+#pragma unroll
+          for (int v = 0; v < NV; ++v) acc[v] = fma(P.lam_a[LPF * D + q], l[q][v], acc[v]);
+        }
+      }
+
+      // C) split adjoint and flux transpose per owned cell
+      if (own) {
+        const int base = (D == 0 ? a0 : D == 1 ? a1 : a2) * PS + S::PENC(D, a0, a1, a2);
+        PrimD w;
+        prim_from<NDIM, MHD>(uo, ri, pr, w);
         double lF[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
           lF[v] = sMu[(0 * NV + v) * TD * PS + base];
           const double dF = sMu[(1 * NV + v) * TD * PS + base];
-          nu[r][v] = fma(0.5 * c, dF, nu[r][v]);
-          cp[D] = fma(0.5 * uo[r][v], dF, cp[D]);
+          nu[v] = fma(0.5 * c, dF, nu[v]);
+          cp[D] = fma(0.5 * uo[v], dF, cp[D]);
         }
-        flux_vjp<NDIM, MHD, D>(uo[r], wo[r], gamma, lF, nu[r]);
+        flux_vjp<NDIM, MHD, D>(uo, w, gamma, lF, nu);
       }
       __syncthreads();
     });
+    // the terms beyond those
+    for (int q = LPF * NDIM; q < P.nlam; ++q) {
+      double l[NV];
+      load_own(T, P.lam_src[q], l);
+#pragma unroll
+      for (int v = 0; v < NV; ++v) acc[v] = fma(P.lam_a[q], l[v], acc[v]);
+    }
 
     // dst = sum_q lam_a[q] lam_q + scale * nu
+    if (own) {
+      const cptr<VjpSide> sd = &T->side[6];
+      gptr_w p = (gptr_w)(slot(P.dst) + (sd->slot + (a0 + a1 * sd->s1 + a2 * sd->s2)));
+      const long long vs = sd->vs;
 #pragma unroll
-    for (int r = 0; r < CPT; ++r) {
-      if (!own[r]) continue;
-      long long ws;
-      gptr_w p = cell_addr_w(st, B, P.dst, oc[r][0], oc[r][1], oc[r][2], ws);
-#pragma unroll
-      for (int v = 0; v < NV; ++v) p[v * ws] = fma(P.scale, nu[r][v], acc[r][v]);
+      for (int v = 0; v < NV; ++v) p[v * vs] = fma(P.scale, nu[v], acc[v]);
     }
   }
   // per-work-group c_max adjoint sums
@@ -891,7 +993,15 @@ __global__ void __launch_bounds__(256) k_lam_export(StateTable st, double* const
 
 template <int NDIM, bool MHD, int TX, int TY, int TZ, int NT>
 static void launch_vjp_t(const VjpParams& p, int grid, hipStream_t s) {
-  hipLaunchKernelGGL((k_vjp<NDIM, MHD, TX, TY, TZ, NT>), dim3(grid), dim3(NT), 0, s, p);
+  // no stage enters more than two later ones through L (RK3, SSPRK(4,3): one)
+  if (p.nmu == 1) hipLaunchKernelGGL((k_vjp<NDIM, MHD, TX, TY, TZ, NT, 1>), dim3(grid), dim3(NT), 0, s, p);
+  else hipLaunchKernelGGL((k_vjp<NDIM, MHD, TX, TY, TZ, NT, 2>), dim3(grid), dim3(NT), 0, s, p);
+}
+
+void launch_vjp_info(const BlockDev* blocks, const Tile* tiles, VjpInfo* info, int ntiles, int ndim, int tx, int ty,
+                     int tz, hipStream_t s) {
+  hipLaunchKernelGGL(k_vjp_info, dim3((ntiles + 63) / 64), dim3(64), 0, s, blocks, tiles, info, ntiles, ndim, tx, ty,
+                     tz);
 }
 
 
@@ -909,7 +1019,7 @@ static void launch_ghost_t(const VjpParams& p, const FixedFace* faces, int nface
 }
 
 #define AMRVAC_VJP(ND, M, TX, TY, TZ, NT)                                                               \
-  {ND, M, TX, TY, TZ, NT, (const void*)&k_vjp<ND, M, TX, TY, TZ, NT>, &launch_vjp_t<ND, M, TX, TY, TZ, NT>, \
+  {ND, M, TX, TY, TZ, NT, (const void*)&k_vjp<ND, M, TX, TY, TZ, NT, 2>, &launch_vjp_t<ND, M, TX, TY, TZ, NT>, \
    &launch_cmax_term_t<ND, M>, &launch_ghost_t<ND, M>}
 
 // The VJP walks a tile list of its own shape (the recompute's list has the

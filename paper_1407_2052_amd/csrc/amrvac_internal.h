@@ -239,6 +239,30 @@ struct FixedFace {
   int face;   // 2 d + side
 };
 
+// What the VJP needs of a tile: as TileInfo, for scratch slots, with the code
+// words of each side.  side: the halos (3 rows from row -3, or from the first
+// row above the tile), and the tile's own cells (6).
+struct VjpSide {
+  long long slot, code, vs;   // first cell in a slot and in a code plane, variable stride
+  int s1, s2;
+  int fixed;                  // no neighbour: no mu
+  int pad_;
+};
+struct alignas(64) VjpInfo {
+  int block;
+  int e[3];                   // cells per direction
+  int rem[3];                 // rows of the upper halo that are the block's own
+  int n0, n1;                 // block extents
+  int p1, p2;                 // padded strides
+  int pad_;
+  double idx[3];
+  long long org;              // first cell's index in the block
+  long long face[3];          // code word above the tile on a fixed upper face, or -1
+  double* u;                  // first cell in the caller's array
+  long long pvs;
+  VjpSide side[7];
+};
+
 constexpr int MAX_TERMS = 6;
 
 // Parameters of one vector-Jacobian product of L (adjoint of one stage
@@ -251,7 +275,7 @@ constexpr int MAX_TERMS = 6;
 // separate reduction from the per-tile sums written to cpart[tile*3+d].
 struct VjpParams {
   StateTable st;
-  const Tile* tiles;
+  const VjpInfo* info;
   int ntiles;
   Control* ctl;
   double gamma;
@@ -298,6 +322,8 @@ struct CombineParams {
 };
 
 const VjpVariant* vjp_variant(int ndim, int mhd);
+void launch_vjp_info(const BlockDev* blocks, const Tile* tiles, VjpInfo* info, int ntiles, int ndim, int tx, int ty,
+                     int tz, hipStream_t s);
 void launch_combine(const CombineParams& p, int grid, hipStream_t s);
 void launch_lam_import(StateTable st, double* const* ptrs, int nv, int dst, int nblocks, hipStream_t s);
 void launch_lam_export(StateTable st, double* const* ptrs, int nv, int src, int nblocks, const double* gadj,

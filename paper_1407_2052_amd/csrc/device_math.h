@@ -73,6 +73,31 @@ __device__ __forceinline__ gptr_w cell_addr_w(const StateTable& st, const BlockD
   return (gptr_w)cell_addr(st, B, buf, i, j, k, vstride);
 }
 
+template <class T>
+using cptr = const __attribute__((address_space(4))) T*;
+
+// The block table and tile list do not change during a launch: uniform
+// accesses to them are scalar loads.
+template <class T>
+__device__ __forceinline__ cptr<T> constant_ptr(const T* p) {
+  return (cptr<T>)(unsigned long long)p;
+}
+
+// A lane's number, to be treated as new here: what is derived from it is
+// recomputed at its use (a few 32-bit operations) instead of being hoisted out
+// of the tile loop and held, or spilled, across it.
+__device__ __forceinline__ int fresh(int i) {
+  asm volatile("" : "+v"(i));
+  return i;
+}
+
+// A uniform value, kept in scalar registers from here on.
+template <class T>
+__device__ __forceinline__ T held(T x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
 // Load all NV variables of cell (i,j,k) of block blk, where only coordinate
 // D may lie outside [0, n_D): then the value comes from the face neighbour's
 // interior (same buffer), or from this block's fixed ghost layer (buffer 0).

@@ -36,16 +36,6 @@ namespace amrvac {
 
 namespace {
 
-template <class T>
-using cptr = const __attribute__((address_space(4))) T*;
-
-// The block table and tile list do not change during a launch: uniform
-// accesses to them are scalar loads.
-template <class T>
-__device__ __forceinline__ cptr<T> constant_ptr(const T* p) {
-  return (cptr<T>)(unsigned long long)p;
-}
-
 // Address of a table entry's first cell in buffer `buf`.
 __device__ __forceinline__ gptr side_addr(const StateTable& st, cptr<TileSide> s, int buf) {
   return s->rel ? (gptr)st.scr + ((long long)(buf - 1) * st.slot_stride + s->addr) : (gptr)(unsigned long long)s->addr;
@@ -57,21 +47,6 @@ __device__ __forceinline__ double load_at(gptr base, unsigned off) {
 }
 __device__ __forceinline__ void store_at(gptr_w base, unsigned off, double x) {
   *(gptr_w)((__attribute__((address_space(1))) char*)base + off * 8u) = x;
-}
-
-// A lane's number, to be treated as new here: what is derived from it is
-// recomputed at its use (a few 32-bit operations) instead of being hoisted out
-// of the tile loop and held, or spilled, across it.
-__device__ __forceinline__ int fresh(int i) {
-  asm volatile("" : "+v"(i));
-  return i;
-}
-
-// A uniform value, kept in scalar registers from here on.
-template <class T>
-__device__ __forceinline__ T held(T x) {
-  asm volatile("" : "+s"(x));
-  return x;
 }
 
 // x of lanes 0-31 beside y of lanes 0-31 (result x), and x of lanes 32-63
