@@ -637,6 +637,14 @@ __device__ __forceinline__ unsigned long long partner_bits(unsigned long long x)
   return ((unsigned long long)b << 32) | a;
 }
 
+// x of the first lane, in scalar registers.
+__device__ __forceinline__ double uniform(double x) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // c_max of a slot, per direction (0 for inactive ones): the maximum over its
 // parts, formed by every wavefront for itself (all lanes active).
 template <int NDIM>
@@ -654,11 +662,7 @@ __device__ __forceinline__ void load_cmax(const Control* ctl, int slot, double* 
     }
   });
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)x[d]);
-    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(x[d] >> 32));
-    c[d] = __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-  }
+  for (int d = 0; d < 3; ++d) c[d] = uniform(__longlong_as_double((long long)x[d]));
 }
 
 // Folds a work-group's maximum along d into a slot.

@@ -62,9 +62,9 @@ namespace amrvac {
 // ---------------------------------------------------------------------------
 // LDS doubles of direction D in a run form with the interface fluxes (and
 // code bytes) beside the split fluxes of the extended box.
-template <class S, int VPG, int XP, bool CODES>
+template <class S, int VPF, int VPG, int XP, bool CODES>
 constexpr int side_by_side(int D) {
-  return 2 * VPG * (D == 0 ? XP * S::T(1) * S::T(2) : S::NEXT(D)) + (VPG + (CODES ? 1 : 0)) * S::NIFC(D);
+  return 2 * VPF * (D == 0 ? XP * S::T(1) * S::T(2) : S::NEXT(D)) + (VPG + (CODES ? 1 : 0)) * S::NIFC(D);
 }
 
 // Runs per pencil of nif interfaces, for npen pencils over all variables and
@@ -92,6 +92,17 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
   using S = TileShape<TX, TY, TZ, HG>;
   constexpr int NV = E::NV;
   constexpr int VPG = (NV + NGRP - 1) / NGRP;
+  // Variables whose split fluxes are reconstructed.  GLM with MP5: psi's are
+  // phi+- = c_h^2 B_D +- c_h psi = +- c_h (psi +- c_h B_D), the multiples +-
+  // c_h of those of B_D (whose physical flux is psi), and MP5 is homogeneous,
+  // so R+ and R- of B_D give both: their sum is its flux, c_h times their
+  // difference psi's.  LIM03's asymptotic switch is not homogeneous.
+  // The MP5 arithmetic bounds this form (vector units busy most of the time at
+  // 2 wavefronts per SIMD): 128^3, one SSPRK(5,4) step, 3.46 -> 2.49 ms with 8
+  // reconstructions instead of 9 and the default tile 8x8x4 (8x8x8 2.63).
+  constexpr bool PSI_FROM_BD = GLM && !LIM;
+  static_assert(!PSI_FROM_BD || (NGRP == 1 && RUNS), "GLM + MP5 is built as a run form with one variable group");
+  constexpr int VPF = PSI_FROM_BD ? 8 : VPG;
   constexpr int TC = S::TC;
   constexpr int CPT = (TC + NT - 1) / NT;
   // with RUNS the x rows of the extended box get an odd LDS stride
@@ -106,7 +117,7 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
   constexpr bool CODE_LDS = EMIT && RUNS && NGRP == 1;
   static_assert(!EMIT || CODE_LDS, "the code-emitting forms are run forms with one variable group");
   static_assert(!CODE_LDS || NV <= 8, "8 code bytes per interface");
-  constexpr int LDS_BASE = cmax_i<2 * VPG * EXT, VPG * IFC + (CODE_LDS ? IFC : 0)>::v;
+  constexpr int LDS_BASE = cmax_i<2 * VPF * EXT, VPG * IFC + (CODE_LDS ? IFC : 0)>::v;
   // Run forms: the interface fluxes (and codes) of a direction go to the top
   // of the array when they fit beside that direction's split fluxes; then the
   // barrier between the reconstructions and their store is not needed, nor
@@ -117,9 +128,9 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
   constexpr int WG_BASE = 20480 / LDS_BASE;
   constexpr int WG_AIM = cmax_i<WPE * 4 / (NT / 64), 1>::v;
   constexpr int LDS_LIMIT = 20480 / (WG_BASE < WG_AIM ? WG_BASE : WG_AIM);
-  constexpr int SB0 = side_by_side<S, VPG, XP, CODE_LDS>(0);
-  constexpr int SB1 = NDIM >= 2 ? side_by_side<S, VPG, XP, CODE_LDS>(1) : 0;
-  constexpr int SB2 = NDIM >= 3 ? side_by_side<S, VPG, XP, CODE_LDS>(2) : 0;
+  constexpr int SB0 = side_by_side<S, VPF, VPG, XP, CODE_LDS>(0);
+  constexpr int SB1 = NDIM >= 2 ? side_by_side<S, VPF, VPG, XP, CODE_LDS>(1) : 0;
+  constexpr int SB2 = NDIM >= 3 ? side_by_side<S, VPF, VPG, XP, CODE_LDS>(2) : 0;
   constexpr int PAD = !(RUNS && NGRP == 1) ? 0
                       : cmax_i<cmax_i<SB0 <= LDS_LIMIT ? SB0 : 0, SB1 <= LDS_LIMIT ? SB1 : 0>::v,
                                SB2 <= LDS_LIMIT ? SB2 : 0>::v;
@@ -207,12 +218,12 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
       constexpr int SD = (D == 0) ? 1 : (D == 1) ? E0P : E0P * E1;
       // interface fluxes at lds[RB ..]: beside the split fluxes (DISJ) or over them
       constexpr int RES_SPAN = VPG * NIFC_D + (CODE_LDS ? NIFC_D : 0);
-      constexpr bool DISJ = RUNS && NGRP == 1 && 2 * VPG * NEXTP + RES_SPAN <= LDS_N;
+      constexpr bool DISJ = RUNS && NGRP == 1 && 2 * VPF * NEXTP + RES_SPAN <= LDS_N;
       constexpr int RB = DISJ ? LDS_N - RES_SPAN : 0;
       // what is written to LDS after phase C: the next direction's split
       // fluxes, or the next tile's first ones and the closing reduction
       constexpr int DN = D + 1 < NDIM ? D + 1 : 0;
-      constexpr int NEXT_SPAN = cmax_i<2 * VPG * (DN == 0 ? XP : S::E(DN, 0)) * S::E(DN, 1) * S::E(DN, 2),
+      constexpr int NEXT_SPAN = cmax_i<2 * VPF * (DN == 0 ? XP : S::E(DN, 0)) * S::E(DN, 1) * S::E(DN, 2),
                                        3 * (NT / 64)>::v;
       constexpr bool SKIP_C_BARRIER = DISJ && NEXT_SPAN <= RB;
       const double c = cin[D];
@@ -252,11 +263,11 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
           }
           const int el = a[0] + E0P * (a[1] + E1 * a[2]);
 #pragma unroll
-          for (int vg = 0; vg < VPG; ++vg) {
+          for (int vg = 0; vg < VPF; ++vg) {
             const int v = G * VPG + vg;
             if (v < NV) {
               lds[vg * NEXTP + el] = fma(c, u[v], F[v]);
-              lds[(VPG + vg) * NEXTP + el] = fma(-c, u[v], F[v]);
+              lds[(VPF + vg) * NEXTP + el] = fma(-c, u[v], F[v]);
             }
           }
         };
@@ -344,11 +355,11 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
           // the pencil's last interface.
           constexpr int NIF = S::T(D) + 1;
           constexpr int NPEN = NIFC_D / NIF;
-          constexpr int NRUN = runs_per_pencil(NIF, VPG * NPEN, NT, EMIT ? 5 : NIF);
+          constexpr int NRUN = runs_per_pencil(NIF, VPF * NPEN, NT, EMIT ? 5 : NIF);
           constexpr int RUN = (NIF + NRUN - 1) / NRUN;
-          constexpr int NIT = VPG * NPEN * NRUN;
+          constexpr int NIT = VPF * NPEN * NRUN;
           constexpr int IPR = (NIT + NT - 1) / NT;
-          double res[IPR][RUN];
+          double res[IPR][RUN], psi[PSI_FROM_BD ? IPR : 1][RUN];
           unsigned char cbyte[CODE_LDS ? IPR : 1][RUN];
 #pragma unroll
           for (int r = 0; r < IPR; ++r) {
@@ -399,12 +410,16 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
             {
               double fw[W], o[RUN];
 #pragma unroll
-              for (int m = 0; m < W; ++m) fw[m] = lds[(VPG + vg) * NEXTP + eb + (W - m) * SD];
+              for (int m = 0; m < W; ++m) fw[m] = lds[(VPF + vg) * NEXTP + eb + (W - m) * SD];
               if constexpr (LIM) {
 #pragma unroll
                 for (int kk = 0; kk < RUN; ++kk) o[kk] = lim03_eval<EMIT>(fw[kk], fw[kk + 1], fw[kk + 2], kr, cm[kk]);
               } else {
                 mp5_run<RUN, EMIT>(fw, o, cm);
+              }
+              if constexpr (PSI_FROM_BD) {
+#pragma unroll
+                for (int kk = 0; kk < RUN; ++kk) psi[r][kk] = c * (res[r][kk] - o[RUN - 1 - kk]);
               }
 #pragma unroll
               for (int kk = 0; kk < RUN; ++kk) res[r][kk] = res[r][kk] + o[RUN - 1 - kk];
@@ -431,6 +446,12 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
             constexpr int SI = S::SI(D);
 #pragma unroll
             for (int kk = 0; kk < RUN; ++kk) lds[RB + vg * NIFC_D + q0 + kk * SI] = res[r][kk];
+            if constexpr (PSI_FROM_BD) {
+              if (vg == 5 + D) {
+#pragma unroll
+                for (int kk = 0; kk < RUN; ++kk) lds[RB + 8 * NIFC_D + q0 + kk * SI] = psi[r][kk];
+              }
+            }
             if constexpr (CODE_LDS) {
               if ((G * VPG + vg) < NV) {
                 unsigned char* lc = reinterpret_cast<unsigned char*>(lds + RB + VPG * NIFC_D);
@@ -492,7 +513,7 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
                   eb = ea[0] + E0P * (ea[1] + E1 * ea[2]);
                 }
                 const double* fp = &lds[vg * NEXTP + eb];
-                const double* fm = &lds[(VPG + vg) * NEXTP + eb];
+                const double* fm = &lds[(VPF + vg) * NEXTP + eb];
                 if constexpr (LIM) {
                   // F+ from cells a_D - 2 .. a_D, F- mirrored from a_D + 1 .. a_D - 1
                   res[r] = lim03(fp[0], fp[SD], fp[2 * SD], kr) + lim03(fm[3 * SD], fm[2 * SD], fm[SD], kr);
