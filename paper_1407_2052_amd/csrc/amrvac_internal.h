@@ -157,6 +157,8 @@ struct StageParams {
   double* cm_hist;
 };
 
+struct LineParams;
+
 // One compiled form of the fused stage kernel (a tile shape and its
 // options): its table entry, shared by the kernel file that instantiates it
 // and the runtime that selects it.
@@ -166,12 +168,21 @@ struct StageVariant {
   const void* fn;
   void (*launch)(const StageParams&, int grid, hipStream_t);
   const char* name;
+  // info > 0: fills the table of a tile list
+  void (*make_info)(const BlockDev* blocks, const Tile* tiles, TileInfo* table, int ntiles, int ndim, int hg, int tx,
+                    int ty, int tz, hipStream_t s) = nullptr;
+  // 1D, if set: whole runs of steps of a small list in one launch, and what
+  // comes before the first such launch
+  hipError_t (*line)(bool mhd, bool lim, const LineParams& p, size_t lds, hipStream_t s) = nullptr;
+  hipError_t (*prepare_line)(bool mhd, bool lim, int run) = nullptr;
 };
 
 const StageVariant* tile_variants(int* count);   // stage_tile.hip
 const StageVariant* tile_emit_variant(int ndim, int mhd, int rec);   // stage_emit.hip, or nullptr
 void launch_tile_info(const BlockDev* blocks, const Tile* tiles, TileInfo* info, int ntiles, int ndim, int hg, int tx,
                       int ty, int tz, hipStream_t s);
+hipError_t launch_line(bool mhd, bool lim, const LineParams& p, size_t lds, hipStream_t s);   // line.hip
+hipError_t prepare_line(bool mhd, bool lim, int run);
 
 struct CmaxParams {
   StateTable st;

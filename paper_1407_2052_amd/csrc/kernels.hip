@@ -1027,6 +1027,12 @@ const StageVariant* stage_variants(int* count) {
     const StageVariant* t = tile_variants(&n);
     std::vector<StageVariant> v(t, t + n);
     v.insert(v.end(), std::begin(g_variants), std::end(g_variants));
+    for (StageVariant& q : v) {
+      if (q.info > 0) q.make_info = launch_tile_info;
+      if (q.ndim != 1) continue;
+      q.line = launch_line;
+      q.prepare_line = prepare_line;
+    }
     return v;
   }();
   *count = (int)all.size();

@@ -303,8 +303,8 @@ static amrvac_status build_tiles(amrvac_ctx* c) {
   c->d_info = nullptr;
   if (V->info > 0) {
     HIP_TRY(c, hipMalloc(&c->d_info, sizeof(TileInfo) * c->htiles.size()));
-    launch_tile_info(c->d_blocks, c->d_tiles, c->d_info, (int)c->htiles.size(), c->cfg.ndim, V->info, V->tx, V->ty,
-                     V->tz, c->stream);
+    V->make_info(c->d_blocks, c->d_tiles, c->d_info, (int)c->htiles.size(), c->cfg.ndim, V->info, V->tx, V->ty,
+                 V->tz, c->stream);
     HIP_TRY(c, hipGetLastError());
   }
   if (c->d_ptiles) (void)hipFree(c->d_ptiles);
@@ -770,7 +770,7 @@ static amrvac_status build_line(amrvac_ctx* c) {
   c->line_length = length;
   c->line_nifc = nifc;
   c->line_lds = line_lds(c, length, nifc);
-  HIP_TRY(c, prepare_line(mhd, lim, RUN));
+  HIP_TRY(c, c->var->prepare_line(mhd, lim, RUN));
   HIP_TRY(c, hipMalloc(&c->d_line_cells, sizeof(LineCell) * c->hline_cells.size()));
   HIP_TRY(c, hipMalloc(&c->d_line_runs, sizeof(LineRun) * c->hline_runs.size()));
   HIP_TRY(c, hipMemcpyAsync(c->d_line_cells, c->hline_cells.data(), sizeof(LineCell) * c->hline_cells.size(),
@@ -1172,7 +1172,7 @@ static amrvac_status line_steps(amrvac_ctx* c, int scheme, double cfl, const dou
   for (int done = 0; done < nsteps; done += LINE_STEPS) {
     p.first = done == 0 ? 1 : 0;
     p.nsteps = std::min(LINE_STEPS, nsteps - done);
-    HIP_TRY(c, launch_line(c->cfg.physics == AMRVAC_MHD, c->cfg.recon == AMRVAC_LIM03, p, c->line_lds, c->stream));
+    HIP_TRY(c, c->var->line(c->cfg.physics == AMRVAC_MHD, c->cfg.recon == AMRVAC_LIM03, p, c->line_lds, c->stream));
   }
   return AMRVAC_OK;
 }

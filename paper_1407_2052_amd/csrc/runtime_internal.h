@@ -25,9 +25,6 @@ void launch_set_control(Control* ctl, double dt_fixed, double cfl, double t, hip
 void launch_copy_interior(const StateTable& st, const Tile* tiles, int ntiles, int tx, int ty, int tz, int nv,
                           int src, int dst, int grid, hipStream_t s);
 
-hipError_t launch_line(bool mhd, bool lim, const LineParams& p, size_t lds, hipStream_t s);
-hipError_t prepare_line(bool mhd, bool lim, int run);
-
 // A range of the tile list that one batched stage launch covers.
 struct LaunchGroup {
   int tile_begin, ntiles, grid;
