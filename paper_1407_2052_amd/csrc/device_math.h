@@ -130,43 +130,65 @@ __device__ __forceinline__ void load_cell(const StateTable& st, int blk, int buf
   for (int v = 0; v < NV; ++v) u[v] = p[v * vs];
 }
 
-// As load_cell, for the variables V0 .. V0+VN-1 only.
-template <int V0, int VN, int D>
-__device__ __forceinline__ void load_cell_vars(const StateTable& st, int blk, int buf, int i, int j, int k,
-                                               double* u) {
-  const BlockDev* B = &st.blocks[blk];
-  int c[3] = {i, j, k};
-  int bf = buf;
-  if (c[D] < 0) {
-    int nb = B->nbr[2 * D];
-    if (nb >= 0) {
-      B = &st.blocks[nb];
-      c[D] += B->n[D];
-    } else {
-      bf = 0;
-    }
-  } else if (c[D] >= B->n[D]) {
-    int nb = B->nbr[2 * D + 1];
-    if (nb >= 0) {
-      c[D] -= B->n[D];
-      B = &st.blocks[nb];
-    } else {
-      bf = 0;
+// Where the cells along direction D of one block lie: below it, in it, above
+// it (the face neighbour's interior, or the block's own fixed ghost layers in
+// buffer 0), each with coordinates counted from this block's first cell.  All
+// uniform, so that a lane's loads need selections but no lookups of their own
+// and can all be in flight together.
+template <int D>
+struct SideRows {
+  gptr p[3];
+  int n0[3], n1[3];   // cells per row, rows per plane
+  long long vs[3];
+  int n;              // cells of this block along D
+
+  __device__ __forceinline__ SideRows(const StateTable& st, int blk, int buf) {
+    const cptr<BlockDev> blocks = constant_ptr(st.blocks);
+    const cptr<BlockDev> B = blocks + blk;
+    n = B->n[D];
+#pragma unroll
+    for (int side = 0; side < 3; ++side) {
+      const int nb = side == 1 ? blk : B->nbr[2 * D + side / 2];
+      const bool fixed = nb < 0;
+      const cptr<BlockDev> N = fixed ? B : blocks + nb;
+      const int shift = side == 1 || fixed ? 0 : side == 0 ? N->n[D] : -n;
+      if (buf == 0 || fixed) {
+        n0[side] = N->P[0];
+        n1[side] = N->P[1];
+        vs[side] = (long long)N->P[0] * N->P[1] * N->P[2];
+        p[side] = (gptr)N->u + (((long long)N->g[2] * N->P[1] + N->g[1]) * N->P[0] + N->g[0]);
+      } else {
+        n0[side] = N->n[0];
+        n1[side] = N->n[1];
+        vs[side] = N->cells;
+        p[side] = (gptr)st.scr + ((long long)(buf - 1) * st.slot_stride + N->off);
+      }
+      p[side] += shift * (D == 0 ? 1ll : D == 1 ? (long long)n0[side] : (long long)n0[side] * n1[side]);
     }
   }
-  long long vs;
-  gptr p = cell_addr(st, *B, bf, c[0], c[1], c[2], vs);
-#pragma unroll
-  for (int v = 0; v < VN; ++v) u[v] = p[(V0 + v) * vs];
-}
 
-// Value of plane v of a per-cell array (interior layout, block at coff, plane
-// stride `plane`) at cell (i,j,k) of block blk, where only coordinate D may
-// lie outside the block: then the face neighbour's cell (its face must
-// exist).
+  // Variables V0 .. V0+VN-1 of cell (i,j,k), whose coordinate D may lie outside.
+  template <int V0, int VN>
+  __device__ __forceinline__ void load(int i, int j, int k, double* u) const {
+    const int c = D == 0 ? i : D == 1 ? j : k;
+    const bool lo = c < 0, hi = c >= n;
+    // selections of values, not of elements (which would put the arrays in scratch)
+    const auto pick = [&](auto below, auto inside, auto above) { return lo ? below : hi ? above : inside; };
+    const gptr q = pick(p[0], p[1], p[2]);
+    const int q0 = pick(n0[0], n0[1], n0[2]), q1 = pick(n1[0], n1[1], n1[2]);
+    const long long w = pick(vs[0], vs[1], vs[2]);
+    const gptr a = q + (((long long)k * q1 + j) * q0 + i);
+#pragma unroll
+    for (int v = 0; v < VN; ++v) u[v] = a[(V0 + v) * w];
+  }
+};
+
+// The current of cell (i,j,k) of block blk (planes of stride `plane`, interior
+// layout, block at coff), where only coordinate D may lie outside the block:
+// then the face neighbour's cell (its face must exist).
 template <int D>
-__device__ __forceinline__ double load_plane(const StateTable& st, const double* a, long long plane, int v, int blk,
-                                             int i, int j, int k) {
+__device__ __forceinline__ void load_current(const StateTable& st, const double* J, long long plane, int blk, int i,
+                                             int j, int k, double* Jc) {
   const BlockDev* B = &st.blocks[blk];
   int c[3] = {i, j, k};
   if (c[D] < 0) {
@@ -176,7 +198,9 @@ __device__ __forceinline__ double load_plane(const StateTable& st, const double*
     c[D] -= B->n[D];
     B = &st.blocks[B->nbr[2 * D + 1]];
   }
-  return ((gptr)a)[v * plane + B->coff + ((long long)c[2] * B->n[1] + c[1]) * B->n[0] + c[0]];
+  gptr p = (gptr)J + (B->coff + ((long long)c[2] * B->n[1] + c[1]) * B->n[0] + c[0]);
+#pragma unroll
+  for (int v = 0; v < 3; ++v) Jc[v] = p[v * plane];
 }
 
 // ---------------------------------------------------------------------------
