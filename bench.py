@@ -59,10 +59,10 @@ def strip_comments(src):
 
 
 def kernel_source_hash(read=None):
-    """Hash of the code (comments and whitespace aside) of the stage kernel
-    and the runtime that launches it."""
+    """Hash of the code (comments and whitespace aside) of the stage kernels
+    and the runtime that launches them."""
     h = hashlib.sha256()
-    for f in ("kernels.hip", "device_math.h", "runtime.cpp", "amrvac_internal.h"):
+    for f in ("kernels.hip", "stage_tile.h", "stage_tile.hip", "device_math.h", "runtime.cpp", "amrvac_internal.h"):
         path = os.path.join("paper_1407_2052_amd", "csrc", f)
         if read is None:
             with open(os.path.join(ROOT, path)) as fh:
@@ -71,6 +71,11 @@ def kernel_source_hash(read=None):
             src = read(path)
         h.update(strip_comments(src).encode())
     return h.hexdigest()[:16]
+
+
+def stage_kernel(variant):
+    """Kernel template of a tile shape: the role-split form or the general one."""
+    return "k_tile" if "-roles" in variant else "k_stage"
 
 
 def measured_traffic(variant, form):
@@ -673,26 +678,26 @@ def main():
 
     roofline = stage_roofline("mhd3d_uneven4096", cells, stage_s, BYTES_PER_CELL_STEP_MHD3D)
     roofline["traffic"] = measured_traffic(variant, form)
-    roofline["kernel"] = f"k_stage<3,MHD> (fused SSPRK stage), {variant}, {form} launches"
+    roofline["kernel"] = f"{stage_kernel(variant)}<3,MHD> (fused SSPRK stage), {variant}, {form} launches"
     others = {}
     if adjoint:
         c5 = adjoint["forward_cell_updates_per_s"]
         others["mhd3d_periodic256_forward"] = stage_roofline(
             "mhd3d_periodic256", 16 ** 3 * 4096, 16 ** 3 * 4096 / c5 / STAGES, BYTES_PER_CELL_STEP_MHD3D)
-        others["mhd3d_periodic256_forward"]["kernel"] = f"k_stage<3,MHD>, {adjoint['forward_tile_shape']}"
+        others["mhd3d_periodic256_forward"]["kernel"] = f"{stage_kernel(adjoint['forward_tile_shape'])}<3,MHD>, {adjoint['forward_tile_shape']}"
         others["mhd3d_periodic256_forward"]["traffic"] = measured_traffic_other(
             "mhd3d_periodic256", adjoint["forward_tile_shape"])
     if adjoint_2d:
         c4 = adjoint_2d["forward_cell_updates_per_s"]
         others["euler2d_256_forward"] = stage_roofline(
             "euler2d_256", 256 * 256, 256 * 256 / c4 / STAGES, BYTES_PER_CELL_STEP_EULER2D)
-        others["euler2d_256_forward"]["kernel"] = f"k_stage<2,HD>, {adjoint_2d['forward_tile_shape']}"
+        others["euler2d_256_forward"]["kernel"] = f"{stage_kernel(adjoint_2d['forward_tile_shape'])}<2,HD>, {adjoint_2d['forward_tile_shape']}"
         others["euler2d_256_forward"]["traffic"] = measured_traffic_other("euler2d_256", adjoint_2d["forward_tile_shape"])
     if mhd2d:
         others["mhd2d_512_forward"] = stage_roofline(
             "mhd2d_512", mhd2d["cells"], mhd2d["cells"] / mhd2d["cell_updates_per_s"] / STAGES,
             BYTES_PER_CELL_STEP_MHD3D)
-        others["mhd2d_512_forward"]["kernel"] = f"k_stage<2,MHD>, {mhd2d['tile_shape']}"
+        others["mhd2d_512_forward"]["kernel"] = f"{stage_kernel(mhd2d['tile_shape'])}<2,MHD>, {mhd2d['tile_shape']}"
         others["mhd2d_512_forward"]["traffic"] = measured_traffic_other("mhd2d_512", mhd2d["tile_shape"])
 
     cpu = None

@@ -7,7 +7,10 @@
 //     (Sect. 2.1, eq. fdcons) -> stage combination -> |v_d| + c_f,d of the
 //     new state for the next stage's c_max.  Template flags select LIM03,
 //     GLM-MHD (Sect. 4.2, glm3) and Hall MHD (Sect. 4.4), and the
-//     code-emitting form of the adjoint's recompute;
+//     code-emitting form of the adjoint's recompute.  It serves 1D, GLM-MHD,
+//     Hall MHD and blocks of any extent; hydro and ideal MHD in 2D and 3D run
+//     the role-split form of the same stage (k_tile) by default, small 1D
+//     lists whole runs of steps in one launch (k_line);
 //   * k_cmax: c_max of a state (Sect. 2.2);
 //   * k_step_begin: dt from c_max (multi-D form of the Sect. 4.4 bound),
 //     t accumulation, the GLM decay factor and c_max slot resets, so a
@@ -931,12 +934,8 @@ static void launch_stage(const StageParams& p, int grid, hipStream_t s) {
   {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE>, \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE>,                                             \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE}
-// the same with interfaces evaluated in runs along each pencil
-#define AMRVAC_VARIANT_R(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                     \
-  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true>, \
-   &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true>,                                             \
-   #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs"}
-// the same with the owned cells' state kept in registers for the whole tile
+// interfaces in runs along each pencil, the owned cells' state kept in
+// registers for the whole tile
 #define AMRVAC_VARIANT_RC(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                  \
   {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0,                                                                  \
    (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, false, false, false, true>,          \
@@ -954,11 +953,6 @@ static void launch_stage(const StageParams& p, int grid, hipStream_t s) {
    (const void*)&k_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), false, true>,          \
    &launch_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), false, true>,                  \
    #ND "d-hall-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-rec" #REC}
-// LIM03 reconstruction in runs along each pencil
-#define AMRVAC_VARIANT_LR(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                         \
-  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, true>, \
-   &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, true>,                                             \
-   #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-lim03"}
 // LIM03 reconstruction
 #define AMRVAC_VARIANT_L(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                            \
   {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, false, true>, \

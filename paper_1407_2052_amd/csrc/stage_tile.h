@@ -23,8 +23,9 @@
 // Measured per SSPRK(5,4) + MP5 step, the best k_stage form against this one:
 // 256^3 MHD 13.4 -> 11.9 ms, uneven 4096-block list 20.4 -> 19.5 ms, 2D MHD
 // 512^2 (4 steps) 0.77 -> 0.66 ms, 2D Euler 256^2 (20 steps) 1.56 -> 1.41 ms;
-// RK3 + LIM03 on 1024 uneven blocks (2 steps) 5.03 -> 4.05 ms.  The VALU is
-// then busy 60 % of the cycles (45 % before) with 2940 instructions per cell
+// RK3 + LIM03 on 1024 uneven blocks (2 steps) 5.03 -> 4.05 ms.  (With c_max in
+// 32 parts, shuffle-free reductions and the x row stride below: 11.1, 18.5,
+// 0.52, 0.89 and 3.92 ms.)  The VALU is then busy 60 % of the cycles (45 % before) with 2940 instructions per cell
 // and stage; 8x8x8 tiles of 1024 threads, one work-group per CU, take 12.9 ms
 // on the 256^3 list: fewer halo cells, but nothing runs during its barriers.
 #pragma once
