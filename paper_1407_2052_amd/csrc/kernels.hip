@@ -25,8 +25,8 @@
 //      LIM03; halo cells come from the neighbour's interior or the fixed
 //      ghost layers) into LDS,
 //   B) evaluates R(F+) + R(F-) for every (interface, variable) of the tile
-//      (T_d + 1 interfaces per pencil), per interface or in runs of up to 5
-//      interfaces per pencil, into registers, then LDS,
+//      (T_d + 1 interfaces per pencil), per interface or in runs of
+//      interfaces along each pencil, into registers, then LDS,
 //   C) accumulates -(Fhat_{i+1/2} - Fhat_{i-1/2}) / dx_d into per-thread
 //      register accumulators of the cells it owns.
 // In the run forms the interface fluxes of B go beside the split fluxes of A
