@@ -103,8 +103,12 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
   // The MP5 arithmetic bounds this form (vector units busy most of the time at
   // 2 wavefronts per SIMD): 128^3, one SSPRK(5,4) step, 3.46 -> 2.49 ms with 8
   // reconstructions instead of 9 and the default tile 8x8x4 (8x8x8 2.63).
-  constexpr bool PSI_FROM_BD = GLM && !LIM;
-  static_assert(!PSI_FROM_BD || (NGRP == 1 && RUNS), "GLM + MP5 is built as a run form with one variable group");
+  // With several variable groups B_D and psi are not reconstructed together:
+  // psi's place holds B_D's split fluxes too, and its reconstructions are
+  // differenced (the same bits, for a ninth reconstruction).
+  constexpr bool PSI_FROM_BD = GLM && !LIM && NGRP == 1;
+  constexpr bool PSI_AS_BD = GLM && !LIM && NGRP > 1;
+  static_assert(!GLM || LIM || RUNS, "GLM + MP5 is built as a run form");
   constexpr int VPF = PSI_FROM_BD ? 8 : VPG;
   constexpr int TC = S::TC;
   constexpr int CPT = (TC + NT - 1) / NT;
@@ -271,8 +275,9 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
           for (int vg = 0; vg < VPF; ++vg) {
             const int v = G * VPG + vg;
             if (v < NV) {
-              lds[vg * NEXTP + el] = fma(c, u[v], F[v]);
-              lds[(VPF + vg) * NEXTP + el] = fma(-c, u[v], F[v]);
+              const int w = PSI_AS_BD && v == 8 ? 5 + D : v;
+              lds[vg * NEXTP + el] = fma(c, u[w], F[w]);
+              lds[(VPF + vg) * NEXTP + el] = fma(-c, u[w], F[w]);
             }
           }
         };
@@ -424,8 +429,10 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
 #pragma unroll
                 for (int kk = 0; kk < RUN; ++kk) psi[r][kk] = c * (res[r][kk] - o[RUN - 1 - kk]);
               }
+              const bool psi_item = PSI_AS_BD && G * VPG + vg == 8;
 #pragma unroll
-              for (int kk = 0; kk < RUN; ++kk) res[r][kk] = res[r][kk] + o[RUN - 1 - kk];
+              for (int kk = 0; kk < RUN; ++kk)
+                res[r][kk] = psi_item ? c * (res[r][kk] - o[RUN - 1 - kk]) : res[r][kk] + o[RUN - 1 - kk];
             }
             if constexpr (CODE_LDS) {
 #pragma unroll
@@ -950,8 +957,12 @@ static void launch_stage(const StageParams& p, int grid, hipStream_t s) {
   {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE>, \
    &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE>,                                             \
    #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE}
-// interfaces in runs along each pencil, the owned cells' state kept in
-// registers for the whole tile
+// the same with interfaces evaluated in runs along each pencil
+#define AMRVAC_VARIANT_R(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                     \
+  {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true>, \
+   &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true>,                                             \
+   #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs"}
+// the same with the owned cells' state kept in registers for the whole tile
 #define AMRVAC_VARIANT_RC(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                  \
   {ND, M, 0, 0, TX, TY, TZ, NT, NGRP, WPE, 0,                                                                  \
    (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, false, false, false, true>,          \
@@ -969,6 +980,11 @@ static void launch_stage(const StageParams& p, int grid, hipStream_t s) {
    (const void*)&k_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), false, true>,          \
    &launch_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), false, true>,                  \
    #ND "d-hall-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-rec" #REC}
+// LIM03 reconstruction in runs along each pencil
+#define AMRVAC_VARIANT_LR(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                         \
+  {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, true>, \
+   &launch_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, true, true>,                                             \
+   #ND "d-" #M "-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-lim03"}
 // LIM03 reconstruction
 #define AMRVAC_VARIANT_L(ND, M, TX, TY, TZ, NT, NGRP, WPE)                                                            \
   {ND, M, 1, 0, TX, TY, TZ, NT, NGRP, WPE, 0, (const void*)&k_stage<ND, M, TX, TY, TZ, NT, NGRP, WPE, false, false, true>, \
@@ -993,53 +1009,120 @@ static void launch_stage(const StageParams& p, int grid, hipStream_t s) {
    &launch_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), false, true, true>,           \
    #ND "d-hall-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-rec" #REC "-core"}
 
-// Tile shapes the autotuner chooses from (the first of each (ndim,
-// physics) is the default).  WPE = minimum waves per SIMD requested from
-// the register allocator.
+static StageVariant preferred(StageVariant v) {
+  v.preferred = true;
+  return v;
+}
+
+// The general tile shapes, which callers select by their position here and
+// saved tuning choices by name.  Which one is fastest depends on the list (its
+// block sizes, how many tiles it has), and the autotuner times them all: on 60
+// blocks of 5-20 x 19 x 11 cells an RK3 step of 3D MHD takes 125 us with
+// 8x4x4 tiles and with the role-split form alike, of 2D hydro with LIM03 (60
+// blocks of 5-39 x 152) 53.7 us with the general form against 55.3.  Of each
+// (ndim, physics, reconstruction) the one marked preferred, else the first,
+// serves where no role-split form does (2D GLM, the same blocks: 101 us, the
+// first shape 152; 1D MHD with LIM03, 60 blocks of 20-399: 33 against 40).
+// WPE = minimum waves per SIMD requested from the register allocator.
 static const StageVariant g_variants[] = {
     // 1D
     AMRVAC_VARIANT(1, false, 128, 1, 1, 128, 1, 1),
+    AMRVAC_VARIANT(1, false, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_RC(1, false, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT(1, true, 128, 1, 1, 128, 1, 1),
+    AMRVAC_VARIANT(1, true, 64, 1, 1, 64, 1, 1),
+    AMRVAC_VARIANT_R(1, true, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_RC(1, true, 64, 1, 1, 64, 1, 1),
-    // 2D and 3D: the role-split forms are faster; these have no limit on the
-    // extents of a block
-    AMRVAC_VARIANT_RC(2, false, 16, 16, 1, 256, 1, 2),
-    AMRVAC_VARIANT_RC(2, true, 16, 16, 1, 256, 1, 2),
+    // 2D
+    AMRVAC_VARIANT(2, false, 16, 16, 1, 256, 1, 1),
+    AMRVAC_VARIANT(2, false, 16, 16, 1, 256, 1, 3),
+    AMRVAC_VARIANT(2, false, 32, 8, 1, 256, 1, 1),
+    AMRVAC_VARIANT_R(2, false, 16, 16, 1, 256, 1, 1),
+    preferred(AMRVAC_VARIANT_RC(2, false, 16, 16, 1, 256, 1, 2)),
+    AMRVAC_VARIANT(2, true, 16, 16, 1, 256, 2, 1),
+    AMRVAC_VARIANT(2, true, 16, 16, 1, 256, 1, 1),
+    AMRVAC_VARIANT(2, true, 16, 16, 1, 256, 2, 3),
+    AMRVAC_VARIANT(2, true, 32, 8, 1, 256, 2, 1),
+    AMRVAC_VARIANT_R(2, true, 16, 16, 1, 256, 1, 1),
+    AMRVAC_VARIANT_R(2, true, 16, 16, 1, 256, 2, 2),
+    preferred(AMRVAC_VARIANT_RC(2, true, 16, 16, 1, 256, 1, 2)),
+    AMRVAC_VARIANT_RC(2, true, 16, 16, 1, 256, 2, 2),
+    // 3D: the owned-cell (CORE) forms first
     AMRVAC_VARIANT_RC(3, false, 8, 8, 4, 256, 1, 2),
+    AMRVAC_VARIANT(3, false, 8, 8, 8, 512, 2, 1),
+    AMRVAC_VARIANT(3, false, 8, 8, 4, 256, 1, 1),
+    AMRVAC_VARIANT_R(3, false, 8, 8, 4, 256, 1, 2),
     AMRVAC_VARIANT_RC(3, true, 8, 8, 8, 512, 1, 2),
+    AMRVAC_VARIANT_RC(3, true, 8, 8, 4, 256, 1, 2),
+    AMRVAC_VARIANT_RC(3, true, 8, 4, 4, 128, 1, 2),
+    AMRVAC_VARIANT_RC(3, true, 8, 8, 4, 256, 2, 3),
+    AMRVAC_VARIANT_R(3, true, 8, 8, 4, 256, 2, 4),
+    AMRVAC_VARIANT_R(3, true, 8, 8, 4, 256, 2, 3),
+    AMRVAC_VARIANT_R(3, true, 8, 8, 8, 512, 2, 4),
+    AMRVAC_VARIANT_R(3, true, 8, 8, 4, 256, 1, 2),
+    AMRVAC_VARIANT(3, true, 8, 8, 4, 256, 2, 3),
     // LIM03
-    AMRVAC_VARIANT_LRC(1, true, 64, 1, 1, 64, 1, 1),
-    AMRVAC_VARIANT_LRC(2, false, 16, 16, 1, 256, 1, 2),
-    AMRVAC_VARIANT_LRC(2, true, 16, 16, 1, 256, 1, 2),
+    AMRVAC_VARIANT_LR(1, true, 64, 1, 1, 64, 1, 1),
+    preferred(AMRVAC_VARIANT_LRC(1, true, 64, 1, 1, 64, 1, 1)),
+    AMRVAC_VARIANT_LR(2, false, 16, 16, 1, 256, 1, 1),
+    preferred(AMRVAC_VARIANT_LRC(2, false, 16, 16, 1, 256, 1, 2)),
+    AMRVAC_VARIANT_LR(2, true, 16, 16, 1, 256, 1, 1),
+    AMRVAC_VARIANT_LR(2, true, 16, 16, 1, 256, 2, 2),
+    preferred(AMRVAC_VARIANT_LRC(2, true, 16, 16, 1, 256, 1, 2)),
     AMRVAC_VARIANT_LRC(3, false, 8, 8, 4, 256, 1, 2),
-    AMRVAC_VARIANT_LRC(3, true, 8, 8, 8, 512, 1, 2),
+    AMRVAC_VARIANT_LR(3, false, 8, 8, 4, 256, 1, 2),
+    AMRVAC_VARIANT_LRC(3, true, 8, 8, 4, 256, 1, 2),
+    preferred(AMRVAC_VARIANT_LRC(3, true, 8, 8, 8, 512, 1, 2)),
+    AMRVAC_VARIANT_LR(3, true, 8, 8, 4, 256, 2, 4),
+    AMRVAC_VARIANT_LR(3, true, 8, 8, 4, 256, 2, 3),
+    AMRVAC_VARIANT_LR(3, true, 8, 8, 8, 512, 2, 4),
     AMRVAC_VARIANT_L(1, false, 128, 1, 1, 128, 1, 1),
+    AMRVAC_VARIANT_L(1, false, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_L(1, true, 128, 1, 1, 128, 1, 1),
+    AMRVAC_VARIANT_L(1, true, 64, 1, 1, 64, 1, 1),
+    AMRVAC_VARIANT_L(2, false, 16, 16, 1, 256, 1, 1),
+    AMRVAC_VARIANT_L(2, false, 32, 8, 1, 256, 1, 1),
+    AMRVAC_VARIANT_L(2, true, 16, 16, 1, 256, 2, 1),
+    AMRVAC_VARIANT_L(2, true, 16, 16, 1, 256, 1, 1),
+    AMRVAC_VARIANT_L(2, true, 32, 8, 1, 256, 2, 1),
+    AMRVAC_VARIANT_L(3, false, 8, 8, 4, 256, 1, 1),
+    AMRVAC_VARIANT_L(3, false, 8, 8, 8, 512, 2, 1),
+    AMRVAC_VARIANT_L(3, true, 8, 8, 4, 256, 2, 3),
     // GLM-MHD
     AMRVAC_VARIANT_G(1, 0, 64, 1, 1, 64, 1, 1),
-    AMRVAC_VARIANT_GC(2, 0, 16, 16, 1, 256, 1, 2),
+    AMRVAC_VARIANT_G(2, 0, 16, 16, 1, 256, 2, 2),
+    AMRVAC_VARIANT_G(2, 0, 16, 16, 1, 256, 1, 1),
+    preferred(AMRVAC_VARIANT_GC(2, 0, 16, 16, 1, 256, 1, 2)),
     AMRVAC_VARIANT_GC(3, 0, 8, 8, 4, 256, 1, 2),
     AMRVAC_VARIANT_GC(3, 0, 8, 8, 8, 512, 1, 2),
+    AMRVAC_VARIANT_GC(3, 0, 8, 8, 4, 256, 3, 3),
+    AMRVAC_VARIANT_G(3, 0, 8, 8, 4, 256, 2, 3),
+    AMRVAC_VARIANT_G(3, 0, 8, 8, 4, 256, 3, 4),
     AMRVAC_VARIANT_G(1, 1, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_G(2, 1, 16, 16, 1, 256, 2, 2),
     AMRVAC_VARIANT_GC(3, 1, 8, 8, 4, 256, 1, 2),
+    AMRVAC_VARIANT_G(3, 1, 8, 8, 4, 256, 2, 4),
+    AMRVAC_VARIANT_G(3, 1, 8, 8, 4, 256, 2, 3),
     // Hall MHD
     AMRVAC_VARIANT_H(1, 0, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_H(2, 0, 16, 16, 1, 256, 2, 2),
     AMRVAC_VARIANT_HC(3, 0, 8, 8, 4, 256, 1, 2),
+    AMRVAC_VARIANT_H(3, 0, 8, 8, 4, 256, 2, 4),
+    AMRVAC_VARIANT_H(3, 0, 8, 8, 4, 256, 2, 2),
     AMRVAC_VARIANT_H(1, 1, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_H(2, 1, 16, 16, 1, 256, 2, 2),
     AMRVAC_VARIANT_HC(3, 1, 8, 8, 4, 256, 1, 2),
+    AMRVAC_VARIANT_H(3, 1, 8, 8, 4, 256, 2, 4),
 };
 
-// The role-split tile forms (stage_tile.hip) first: the default where they exist.
+// The role-split tile forms (stage_tile.hip), the default where they exist,
+// come after the general ones.
 const StageVariant* stage_variants(int* count) {
   static const std::vector<StageVariant> all = [] {
+    std::vector<StageVariant> v(std::begin(g_variants), std::end(g_variants));
     int n = 0;
     const StageVariant* t = tile_variants(&n);
-    std::vector<StageVariant> v(t, t + n);
-    v.insert(v.end(), std::begin(g_variants), std::end(g_variants));
+    v.insert(v.end(), t, t + n);
     for (StageVariant& q : v) {
       if (q.info > 0) q.make_info = launch_tile_info;
       if (q.ndim != 1) continue;

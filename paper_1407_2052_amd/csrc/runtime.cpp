@@ -155,15 +155,31 @@ bool amrvac::offsets_fit(const amrvac_ctx* c) {
   return true;
 }
 
+// The general form taken where the caller chose none and no role-split form
+// serves.
+static int general_variant(const amrvac_ctx* c) {
+  const int n = count_variants(c);
+  for (int k = 0; k < n; ++k)
+    if (pick_variant(c, k)->preferred) return k;
+  return 0;
+}
+
+// The variant of a context without a choice of the caller's: the first
+// role-split form, else the general one.
+static int default_variant(const amrvac_ctx* c) {
+  const int n = count_variants(c);
+  for (int k = 0; k < n; ++k)
+    if (pick_variant(c, k)->info > 0) return k;
+  return general_variant(c);
+}
+
 // The kernel variant i runs on the current block list: itself, or, for a
-// role-split form on blocks whose rows or planes exceed its offsets, the first
-// form of this context without that limit (the same results bit for bit).
+// role-split form on blocks whose rows or planes exceed its offsets, the
+// general form (the same results bit for bit).
 static const StageVariant* resolve_variant(const amrvac_ctx* c, int i) {
   const StageVariant* v = pick_variant(c, i);
   if (!v || v->info == 0 || offsets_fit(c)) return v;
-  for (int k = 0; k < count_variants(c); ++k)
-    if (pick_variant(c, k)->info == 0) return pick_variant(c, k);
-  return v;
+  return pick_variant(c, general_variant(c));
 }
 
 static amrvac_status select_variant(amrvac_ctx* c, int i);
@@ -804,7 +820,8 @@ amrvac_status amrvac_create(const amrvac_config* cfg, void* hip_stream, amrvac_c
   c->single_launch = cfg->exec == AMRVAC_EXEC_BATCHED_SINGLE;
   c->nvar = cfg->physics == AMRVAC_GLM ? 9 : cfg->physics == AMRVAC_MHD ? 8 : 2 + cfg->ndim;
   c->stream = (hipStream_t)hip_stream;
-  c->var = pick_variant(c, 0);
+  c->var_index = default_variant(c);
+  c->var = pick_variant(c, c->var_index);
   hipError_t e = hipGetDevice(&c->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, c->device);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking);
