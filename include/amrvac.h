@@ -95,9 +95,11 @@ typedef enum { AMRVAC_RK3 = 0, AMRVAC_SSPRK43 = 1, AMRVAC_SSPRK54 = 2 } amrvac_s
  *  BATCHED_SINGLE:  one persistent fused launch per stage over the whole
  *                   list (each XCD's share holds an eighth of every class),
  *                   steps replayed from HIP graphs as for BATCHED.
- * In either batched form a small 1D list (hydro or ideal MHD, at most 1024 or
- * 640 cells with the ghost cells of fixed faces) runs whole steps in one
- * launch of one work-group.
+ * In either batched form a small 1D list (hydro or ideal MHD) runs whole steps
+ * in one launch of one work-group, unless a tile shape was chosen for it: lists
+ * without passive blocks of c cells in b blocks that fit its threads, at most
+ * 1024 (hydro) or 640 (MHD) cells with the 3 ghost cells of every fixed face,
+ * and its 160 KB of LDS, 2 c + 7 b <= 2923 (hydro) or 1204 (MHD).
  * Setting a batched form rebuilds the work list; the autotuner times tile
  * shapes in the form that is set. */
 typedef enum { AMRVAC_EXEC_PER_BLOCK = 0, AMRVAC_EXEC_BATCHED = 1, AMRVAC_EXEC_BATCHED_SINGLE = 2 } amrvac_exec;
@@ -187,11 +189,18 @@ amrvac_status amrvac_set_exec(amrvac_ctx *ctx, int exec);
  * this context's (ndim, physics): their number, the name of shape i (a
  * static string, NULL if i is out of range), and explicit selection of
  * shape i for later calls (rebuilds the work list and drops cached graphs;
- * results are bitwise identical for every shape).  Errors: INVALID. */
+ * results are bitwise identical for every shape).  Two kinds of shape do not
+ * serve every list: "...-line", the one-launch form of small 1D lists (above),
+ * and "...-roles...", for blocks in 2D and 3D whose rows and planes, with ghost
+ * layers, are within 2^28 cells (24 n0, plus 12 n0 n1 in 3D).  They are the
+ * default where they fit; where a chosen one does not, a general shape runs
+ * until a list, execution form or active set that it fits is set.
+ * amrvac_get_variant returns the index of the shape that runs (-1 for NULL
+ * ctx).  Errors: INVALID. */
 int amrvac_num_variants(const amrvac_ctx *ctx);
 const char *amrvac_variant_name(const amrvac_ctx *ctx, int i);
 amrvac_status amrvac_set_variant(amrvac_ctx *ctx, int i);
-int amrvac_get_variant(const amrvac_ctx *ctx);   /* index in use, -1 for NULL ctx */
+int amrvac_get_variant(const amrvac_ctx *ctx);
 
 /* Autotuner: times nsteps steps of `scheme` (CFL 0.4) with every compiled
  * tile shape on the current block list, on scratch copies of the states
@@ -200,7 +209,7 @@ int amrvac_get_variant(const amrvac_ctx *ctx);   /* index in use, -1 for NULL ct
  * for the same (device, ndim, physics, block count, cell count, scheme) is
  * reused without timing and new choices are appended.  ms_out (host, may
  * be NULL, amrvac_num_variants entries) receives the milliseconds per step
- * of each shape (-1 if not timed).  Synchronises the stream.
+ * of each shape (-1 if not timed, as those that do not fit the list).  Synchronises the stream.
  * Errors: INVALID (no blocks, scheme unknown, nsteps < 1), NONPHYSICAL,
  * NOMEM, DEVICE. */
 amrvac_status amrvac_autotune(amrvac_ctx *ctx, int scheme, int nsteps, double *ms_out);

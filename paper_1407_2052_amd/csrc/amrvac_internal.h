@@ -171,8 +171,9 @@ struct StageVariant {
   // info > 0: fills the table of a tile list
   void (*make_info)(const BlockDev* blocks, const Tile* tiles, TileInfo* table, int ntiles, int ndim, int hg, int tx,
                     int ty, int tz, hipStream_t s) = nullptr;
-  // 1D, if set: whole runs of steps of a small list in one launch, and what
-  // comes before the first such launch
+  // 1D, if set: this form runs whole steps of a small list in one launch
+  // (launch and the tile shape then serve right-hand sides), and what comes
+  // before the first such launch
   hipError_t (*line)(bool mhd, bool lim, const LineParams& p, size_t lds, hipStream_t s) = nullptr;
   hipError_t (*prepare_line)(bool mhd, bool lim, int run) = nullptr;
   bool preferred = false;   // among the general forms (info == 0) of its kind
@@ -211,11 +212,13 @@ constexpr int LINE_LDS_BYTES = 160 * 1024;
 constexpr int LINE_STEPS = 64;                // steps per launch
 
 // A cell of the list (then the ghost cells of its fixed faces), one per
-// thread: where its state is, its entry in the lines of split fluxes and up to
-// two halo entries that repeat it, its lower interface, 0.5 / dx.
+// thread: where its state is in the caller's array and in a scratch slot, its
+// entry in the lines of split fluxes and up to two halo entries that repeat it,
+// its lower interface, 0.5 / dx.
 struct LineCell {
   double* u;
   long long vs;
+  long long slot, slot_vs;
   double hidx;
   int pos, dup[2], ifc;
 };
@@ -237,6 +240,7 @@ struct LineStage {
 struct LineParams {
   const LineCell* cells;
   const LineRun* runs;
+  double* slot;                 // advance the state in this scratch slot, or null: the caller's arrays
   Control* ctl;
   double gamma, dt_fixed, cfl, t0, dx_min;
   int ncells, nghost, nruns, length, nifc;

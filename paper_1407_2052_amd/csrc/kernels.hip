@@ -1115,20 +1115,33 @@ static const StageVariant g_variants[] = {
     AMRVAC_VARIANT_H(3, 1, 8, 8, 4, 256, 2, 4),
 };
 
-// The role-split tile forms (stage_tile.hip), the default where they exist,
-// come after the general ones.
+// After the general forms: the role-split tile forms (stage_tile.hip) and, for
+// 1D hydro and ideal MHD, the form that runs a small list in one launch
+// (line.hip), with the preferred general shape for right-hand sides.  They are
+// the default where the list allows them.
 const StageVariant* stage_variants(int* count) {
   static const std::vector<StageVariant> all = [] {
     std::vector<StageVariant> v(std::begin(g_variants), std::end(g_variants));
     int n = 0;
     const StageVariant* t = tile_variants(&n);
     v.insert(v.end(), t, t + n);
-    for (StageVariant& q : v) {
+    for (StageVariant& q : v)
       if (q.info > 0) q.make_info = launch_tile_info;
-      if (q.ndim != 1) continue;
-      q.line = launch_line;
-      q.prepare_line = prepare_line;
-    }
+    static const char* const names[2][2] = {{"1d-false-line", "1d-false-line-lim03"},
+                                            {"1d-true-line", "1d-true-line-lim03"}};
+    for (int mhd = 0; mhd < 2; ++mhd)
+      for (int rec = 0; rec < 2; ++rec) {
+        const StageVariant* base = nullptr;
+        for (const StageVariant& q : v)
+          if (q.ndim == 1 && q.mhd == mhd && q.rec == rec && !q.hall && !q.line)
+            if (!base || (q.preferred && !base->preferred)) base = &q;
+        StageVariant q = *base;
+        q.preferred = false;
+        q.name = names[mhd][rec];
+        q.line = launch_line;
+        q.prepare_line = prepare_line;
+        v.push_back(q);
+      }
     return v;
   }();
   *count = (int)all.size();

@@ -19,8 +19,9 @@
 // ms (5.4 us per stage).  What bounds it now: one CU is all the arithmetic
 // there is (an MHD stage's reconstructions alone take it 2.4 us) and the chain
 // of three barriers, a division and the square roots of the speeds.  The limit
-// is a thread per cell and the fluxes in one CU's LDS, 1024 hydro or 640 MHD
-// cells: at the limit a stage is still shorter than a launch of k_stage.
+// is a thread per cell (and fixed ghost cell) and the fluxes in one CU's LDS: up
+// to 1018 hydro or 598 MHD cells in one block with fixed faces, fewer in many
+// blocks.
 #include "device_math.h"
 
 namespace amrvac {
@@ -48,12 +49,13 @@ __global__ void __launch_bounds__(line_threads(MHD)) k_line(LineParams P) {
   const bool has = tid < P.ncells + P.nghost;
   const double gamma = P.gamma;
   const LineCell me = P.cells[has ? tid : 0];
+  // fixed ghost cells are in the caller's arrays either way
+  const bool in_slot = P.slot != nullptr && cell;
+  const gptr_w state = (gptr_w)(in_slot ? P.slot + me.slot : me.u);
+  const long long vs = in_slot ? me.slot_vs : me.vs;
   double u[NV], U0[NV], S[NV];
-  {
-    gptr p = (gptr)me.u;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) u[v] = p[v * me.vs];
-  }
+  for (int v = 0; v < NV; ++v) u[v] = state[v * vs];
   bool ok_all = true;
   double ri = 1.0, pr = 1.0;   // 1/rho and p of u
   // c_max of the current state, the same in every thread
@@ -145,9 +147,8 @@ __global__ void __launch_bounds__(line_threads(MHD)) k_line(LineParams P) {
     }
   }
   if (cell) {
-    gptr_w p = (gptr_w)me.u;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) p[v * me.vs] = u[v];
+    for (int v = 0; v < NV; ++v) state[v * vs] = u[v];
   }
   if (tid == 0) {
     P.ctl->t = t;

@@ -155,34 +155,35 @@ bool amrvac::offsets_fit(const amrvac_ctx* c) {
   return true;
 }
 
-// The general form taken where the caller chose none and no role-split form
-// serves.
-static int general_variant(const amrvac_ctx* c) {
+// Whether the current block list, execution form and active set allow variant
+// v: the one-launch form needs a list that fits one work-group (build_line), a
+// batched form and no passive block, the role-split forms blocks whose rows and
+// planes are within their offsets.
+static bool variant_fits(const amrvac_ctx* c, const StageVariant* v) {
+  if (v->line) return c->d_line_cells && c->exec == AMRVAC_EXEC_BATCHED && c->n_active == (int)c->hb.size();
+  return v->info == 0 || offsets_fit(c);
+}
+
+// The variant that runs where `want` (-1: no choice of the caller's) is asked
+// for: itself where it fits.  Without a choice the one-launch form, else the
+// first role-split form; where none of these fits the general form (the same
+// results bit for bit).
+static int resolve_variant(const amrvac_ctx* c, int want) {
+  if (want >= 0 && variant_fits(c, pick_variant(c, want))) return want;
   const int n = count_variants(c);
-  for (int k = 0; k < n; ++k)
-    if (pick_variant(c, k)->preferred) return k;
-  return 0;
+  int general = 0;
+  for (int k = n - 1; k >= 0; --k) {
+    const StageVariant* v = pick_variant(c, k);
+    if (v->preferred) general = k;
+  }
+  if (want < 0) {
+    for (int k = 0; k < n; ++k) {
+      const StageVariant* v = pick_variant(c, k);
+      if ((v->line || v->info > 0) && variant_fits(c, v)) return k;
+    }
+  }
+  return general;
 }
-
-// The variant of a context without a choice of the caller's: the first
-// role-split form, else the general one.
-static int default_variant(const amrvac_ctx* c) {
-  const int n = count_variants(c);
-  for (int k = 0; k < n; ++k)
-    if (pick_variant(c, k)->info > 0) return k;
-  return general_variant(c);
-}
-
-// The kernel variant i runs on the current block list: itself, or, for a
-// role-split form on blocks whose rows or planes exceed its offsets, the
-// general form (the same results bit for bit).
-static const StageVariant* resolve_variant(const amrvac_ctx* c, int i) {
-  const StageVariant* v = pick_variant(c, i);
-  if (!v || v->info == 0 || offsets_fit(c)) return v;
-  return pick_variant(c, general_variant(c));
-}
-
-static amrvac_status select_variant(amrvac_ctx* c, int i);
 
 // Build the tile list of the current variant: blocks ordered largest first,
 // then along a Morton curve of their origins; tiles of a block contiguous and
@@ -361,15 +362,21 @@ amrvac_status ensure_slots(amrvac_ctx* c, int n) {
 }
 }  // namespace amrvac
 
-static amrvac_status select_variant(amrvac_ctx* c, int i) {
-  const StageVariant* v = resolve_variant(c, i);
-  if (!v) return fail(c, AMRVAC_ERR_INVALID, "variant %d does not exist", i);
-  c->var_index = i;
-  if (v == c->var && !c->htiles.empty()) return AMRVAC_OK;
+// Makes the variant that runs for the caller's choice the current one.
+// Returns whether the tile list has to be built for it.
+static bool adopt_variant(amrvac_ctx* c) {
+  c->var_index = resolve_variant(c, c->want);
+  const StageVariant* v = pick_variant(c, c->var_index);
+  if (v == c->var) return c->htiles.empty();
   drop_graphs(c);
+  const bool same_tiles = c->var && v->fn == c->var->fn;   // the one-launch form and its general shape
   c->var = v;
-  if (c->hb.empty()) return AMRVAC_OK;
-  return build_tiles(c);
+  return !same_tiles || c->htiles.empty();
+}
+
+static amrvac_status select_variant(amrvac_ctx* c, int want) {
+  c->want = want;
+  return adopt_variant(c) && !c->hb.empty() ? build_tiles(c) : AMRVAC_OK;
 }
 
 namespace amrvac {
@@ -716,7 +723,10 @@ static size_t line_lds(const amrvac_ctx* c, int length, int nifc) {
 static amrvac_status build_line(amrvac_ctx* c) {
   c->hline_cells.clear();
   c->hline_runs.clear();
-  if (c->cfg.ndim != 1 || c->cfg.physics == AMRVAC_GLM || c->cfg.eta_h > 0.0) return AMRVAC_OK;
+  const StageVariant* V = nullptr;   // the one-launch form of this context
+  for (int k = 0; k < count_variants(c) && !V; ++k)
+    if (pick_variant(c, k)->line) V = pick_variant(c, k);
+  if (!V) return AMRVAC_OK;
   const bool mhd = c->cfg.physics == AMRVAC_MHD, lim = c->cfg.recon == AMRVAC_LIM03;
   const int threads = line_threads(mhd);
   if (c->total_cells > threads) return AMRVAC_OK;
@@ -760,6 +770,8 @@ static amrvac_status build_line(amrvac_ctx* c) {
       LineCell k{};
       k.u = D.u + (i + NG);
       k.vs = D.P[0];
+      k.slot = D.off + i;
+      k.slot_vs = D.cells;
       k.hidx = 0.5 * D.inv_dx[0];
       k.pos = base[b] + NG + i;
       k.ifc = ibase[b] + i;
@@ -786,7 +798,7 @@ static amrvac_status build_line(amrvac_ctx* c) {
   c->line_length = length;
   c->line_nifc = nifc;
   c->line_lds = line_lds(c, length, nifc);
-  HIP_TRY(c, c->var->prepare_line(mhd, lim, RUN));
+  HIP_TRY(c, V->prepare_line(mhd, lim, RUN));
   HIP_TRY(c, hipMalloc(&c->d_line_cells, sizeof(LineCell) * c->hline_cells.size()));
   HIP_TRY(c, hipMalloc(&c->d_line_runs, sizeof(LineRun) * c->hline_runs.size()));
   HIP_TRY(c, hipMemcpyAsync(c->d_line_cells, c->hline_cells.data(), sizeof(LineCell) * c->hline_cells.size(),
@@ -795,6 +807,9 @@ static amrvac_status build_line(amrvac_ctx* c) {
                             hipMemcpyHostToDevice, c->stream));
   return AMRVAC_OK;
 }
+
+static amrvac_status line_steps(amrvac_ctx* c, int scheme, double cfl, const double* dt_fixed, int nsteps, double t0,
+                                int buf);
 
 extern "C" {
 
@@ -820,7 +835,7 @@ amrvac_status amrvac_create(const amrvac_config* cfg, void* hip_stream, amrvac_c
   c->single_launch = cfg->exec == AMRVAC_EXEC_BATCHED_SINGLE;
   c->nvar = cfg->physics == AMRVAC_GLM ? 9 : cfg->physics == AMRVAC_MHD ? 8 : 2 + cfg->ndim;
   c->stream = (hipStream_t)hip_stream;
-  c->var_index = default_variant(c);
+  c->var_index = resolve_variant(c, -1);
   c->var = pick_variant(c, c->var_index);
   hipError_t e = hipGetDevice(&c->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, c->device);
@@ -873,7 +888,6 @@ amrvac_status amrvac_set_blocks(amrvac_ctx* c, const amrvac_block* blocks, int n
   drop_graphs(c);
   free_tables(c);
   c->hb.assign(blocks, blocks + nblocks);
-  c->var = resolve_variant(c, c->var_index);
   c->hdev.resize(nblocks);
   c->active.assign(nblocks, 1);
   c->n_active = nblocks;
@@ -936,7 +950,10 @@ amrvac_status amrvac_set_blocks(amrvac_ctx* c, const amrvac_block* blocks, int n
                             c->stream));
   HIP_TRY(c, hipMalloc(&c->d_rhs_ptrs, sizeof(double*) * nblocks));
   amrvac_status st = build_line(c);
-  if (st == AMRVAC_OK) st = build_tiles(c);
+  if (st == AMRVAC_OK) {
+    (void)adopt_variant(c);
+    st = build_tiles(c);
+  }
   if (st != AMRVAC_OK) return st;
   // control: ndx
   Control h{};
@@ -953,13 +970,14 @@ amrvac_status amrvac_set_exec(amrvac_ctx* c, int exec) {
     return fail(c, AMRVAC_ERR_INVALID, "set_exec: unknown execution form %d", exec);
   const bool single = exec == AMRVAC_EXEC_BATCHED_SINGLE;
   c->exec = single ? AMRVAC_EXEC_BATCHED : exec;
+  bool rebuild = adopt_variant(c);
   if (exec != AMRVAC_EXEC_PER_BLOCK && single != c->single_launch) {
     // the launch grouping is part of the work list
     c->single_launch = single;
     drop_graphs(c);
-    if (!c->hb.empty()) return build_tiles(c);
+    rebuild = true;
   }
-  return AMRVAC_OK;
+  return rebuild && !c->hb.empty() ? build_tiles(c) : AMRVAC_OK;
 }
 
 int amrvac_num_variants(const amrvac_ctx* c) { return c ? count_variants(c) : 0; }
@@ -1010,24 +1028,30 @@ amrvac_status amrvac_autotune(amrvac_ctx* c, int scheme, int nsteps, double* ms_
   // time every shape on scratch copies: slot ids 1..3 = A, B, S; 4 = U copy
   amrvac_status st = ensure_slots(c, 4);
   if (st != AMRVAC_OK) return st;
-  const int keep = c->var_index;
+  const int keep = c->want;
   const int keep_exec = c->exec;
   c->exec = AMRVAC_EXEC_BATCHED;
   hipEvent_t e0, e1;
   HIP_TRY(c, hipEventCreate(&e0));
   HIP_TRY(c, hipEventCreate(&e1));
-  int best = keep;
+  int best = c->var_index;
   float best_ms = 1e30f;
   for (int i = 0; i < nv; ++i) {
     st = select_variant(c, i);
-    if (st != AMRVAC_OK) continue;
+    // a form that does not fit the list: the one that runs instead is timed as itself
+    if (st != AMRVAC_OK || c->var_index != i) continue;
     launch_copy_interior(state_table(c), c->d_tiles, (int)c->htiles.size(), c->var->tx, c->var->ty, c->var->tz,
                          c->nvar, 0, 4, std::min<int>(c->ncu * 8, (int)c->htiles.size()), c->stream);
     launch_set_control(c->d_ctl, 0.0, 0.4, 0.0, c->stream);
     launch_cmax_of(c, 4, 0, c->stream, true);
-    enqueue_step(c, scheme, AMRVAC_EXEC_BATCHED, c->stream, 4, 1, 2, 3, 4);   // warm-up
+    auto steps = [&](int n) -> amrvac_status {
+      if (c->var->line) return line_steps(c, scheme, 0.4, nullptr, n, 0.0, 4);
+      for (int it = 0; it < n; ++it) enqueue_step(c, scheme, AMRVAC_EXEC_BATCHED, c->stream, 4, 1, 2, 3, 4);
+      return AMRVAC_OK;
+    };
+    if (steps(1) != AMRVAC_OK) continue;   // warm-up
     HIP_TRY(c, hipEventRecord(e0, c->stream));
-    for (int it = 0; it < nsteps; ++it) enqueue_step(c, scheme, AMRVAC_EXEC_BATCHED, c->stream, 4, 1, 2, 3, 4);
+    if (steps(nsteps) != AMRVAC_OK) continue;
     HIP_TRY(c, hipEventRecord(e1, c->stream));
     HIP_TRY(c, hipEventSynchronize(e1));
     if (hipGetLastError() != hipSuccess) continue;
@@ -1051,7 +1075,7 @@ amrvac_status amrvac_autotune(amrvac_ctx* c, int scheme, int nsteps, double* ms_
   st = select_variant(c, best);
   if (st == AMRVAC_OK && cache && *cache) {
     std::ofstream out(cache, std::ios::app);
-    out << key << " " << c->var->name << "\n";
+    out << key << " " << pick_variant(c, best)->name << "\n";
   }
   return st;
 }
@@ -1150,10 +1174,14 @@ static amrvac_status check_step_args(amrvac_ctx* c, int scheme, double cfl, cons
   return AMRVAC_OK;
 }
 
-// The steps of a small 1D list, LINE_STEPS per launch.
+// The steps of a small 1D list, LINE_STEPS per launch, on buffer `buf`.
 static amrvac_status line_steps(amrvac_ctx* c, int scheme, double cfl, const double* dt_fixed, int nsteps,
-                                double t0) {
+                                double t0, int buf) {
   LineParams p{};
+  if (buf > 0) {
+    const StateTable st = state_table(c);
+    p.slot = st.scr + (buf - 1) * st.slot_stride;
+  }
   p.cells = c->d_line_cells;
   p.runs = c->d_line_runs;
   p.ctl = c->d_ctl;
@@ -1208,8 +1236,8 @@ constexpr int GRAPH_STEPS = 8;
 // form replays a cached graph of GRAPH_STEPS steps.
 static amrvac_status enqueue_steps(amrvac_ctx* c, int scheme, double cfl, const double* dt_fixed, int nsteps,
                                    double* t_inout, bool use_graph) {
-  if (c->d_line_cells && c->exec == AMRVAC_EXEC_BATCHED && c->hptiles.empty() && nsteps > 0)
-    return line_steps(c, scheme, cfl, dt_fixed, nsteps, t_inout ? *t_inout : 0.0);
+  if (c->var->line && nsteps > 0)
+    return line_steps(c, scheme, cfl, dt_fixed, nsteps, t_inout ? *t_inout : 0.0, 0);
   if (!c->hptiles.empty() && nsteps > 0) {
     // passive blocks: their current state in the stage buffers A and B,
     // which active neighbours read as halo at every stage
@@ -1334,6 +1362,7 @@ amrvac_status amrvac_set_active(amrvac_ctx* c, const unsigned char* active) {
   drop_graphs(c);
   c->active = a;
   c->n_active = n;
+  (void)adopt_variant(c);
   amrvac_status st = build_tiles(c);
   if (st != AMRVAC_OK) return st;
   // dt rule over the active blocks' cell widths

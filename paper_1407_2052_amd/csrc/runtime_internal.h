@@ -69,7 +69,8 @@ struct amrvac_ctx {
 
   // tiles of the chosen variant
   const StageVariant* var = nullptr;
-  int var_index = 0;
+  int want = -1;        // the caller's choice of variant, -1: none
+  int var_index = 0;    // of var
   std::vector<Tile> htiles;
   Tile* d_tiles = nullptr;
   amrvac::TileInfo* d_info = nullptr;   // of the same tiles, for variants that read it
