@@ -474,24 +474,28 @@ __global__ void __launch_bounds__(NT, WPE) k_tile(StageParams P) {
         if constexpr (EMIT) {
           // one word per owned cell, the codes of its lower face (low nibbles
           // F+, high nibbles F-; unused bytes of a hydro word unspecified), and
-          // for the last cell below a fixed upper face that face's too
-          if (inside(a)) {
-            const unsigned long long* lc = reinterpret_cast<const unsigned long long*>(lds + CB);
-            const cptr<BlockDev> B = constant_ptr(st.blocks) + T->block;
-            const cptr<TileSide> sd = &T->side[1][6];
-            using cw = __attribute__((address_space(1))) unsigned long long*;
-            const cw plane = (cw)(P.codes + D * P.code_plane);
-            plane[B->coff + T->org + (a[0] + a[1] * sd->s1 + a[2] * sd->s2)] = lc[il] | (lc[NIFC_D + il] << 4);
-            if (B->fco[D] >= 0) {
-              const cptr<Tile> tl = constant_ptr(P.tiles + P.tile_begin) + t;
-              const int ac[3] = {tl->o[0] + a[0], tl->o[1] + a[1], tl->o[2] + a[2]};
-              if (ac[D] == B->n[D] - 1) {
-                const long long tr = D == 0 ? (long long)ac[1] + (long long)B->n[1] * ac[2]
-                                   : D == 1 ? (long long)ac[0] + (long long)B->n[0] * ac[2]
-                                            : (long long)ac[0] + (long long)B->n[0] * ac[1];
-                plane[P.code_faces + B->fco[D] + tr] = lc[il + SI] | (lc[NIFC_D + il + SI] << 4);
-              }
-            }
+          // for the last cell below a fixed upper face that face's too.  The two
+          // stores are conditions beside each other under uniform branches: of a
+          // divergent condition nested in another, both ending at one place, the
+          // compiler restores the lanes of both only after the copies that its
+          // register allocation puts between the two ends, so that they reach
+          // some lanes only (seen in the 2D MHD LIM03 forms: the lane number was
+          // lost on lists with fixed faces).
+          const unsigned long long* lc = reinterpret_cast<const unsigned long long*>(lds + CB);
+          const cptr<BlockDev> B = constant_ptr(st.blocks) + T->block;
+          const cptr<TileSide> sd = &T->side[1][6];
+          using cw = __attribute__((address_space(1))) unsigned long long*;
+          const cw plane = (cw)(P.codes + D * P.code_plane);
+          const bool in = inside(a);
+          if (in) plane[B->coff + T->org + (a[0] + a[1] * sd->s1 + a[2] * sd->s2)] = lc[il] | (lc[NIFC_D + il] << 4);
+          if (B->fco[D] >= 0) {
+            const cptr<Tile> tl = constant_ptr(P.tiles + P.tile_begin) + t;
+            const int ac[3] = {tl->o[0] + a[0], tl->o[1] + a[1], tl->o[2] + a[2]};
+            const long long tr = D == 0 ? (long long)ac[1] + (long long)B->n[1] * ac[2]
+                               : D == 1 ? (long long)ac[0] + (long long)B->n[0] * ac[2]
+                                        : (long long)ac[0] + (long long)B->n[0] * ac[1];
+            const bool last = in & (ac[D] == B->n[D] - 1);
+            if (last) plane[P.code_faces + B->fco[D] + tr] = lc[il + SI] | (lc[NIFC_D + il + SI] << 4);
           }
         }
       }
