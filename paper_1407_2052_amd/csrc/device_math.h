@@ -183,6 +183,23 @@ struct SideRows {
   }
 };
 
+// The rows of every direction, so that the table loads of one direction do not
+// wait for the cells of another.
+template <int NDIM>
+struct AllRows {
+  SideRows<0> x;
+  SideRows<NDIM >= 2 ? 1 : 0> y;
+  SideRows<NDIM >= 3 ? 2 : 0> z;
+  __device__ __forceinline__ AllRows(const StateTable& st, int blk, int buf)
+      : x(st, blk, buf), y(st, blk, buf), z(st, blk, buf) {}
+  template <int D>
+  __device__ __forceinline__ const auto& along() const {
+    if constexpr (D == 0) return x;
+    else if constexpr (D == 1) return y;
+    else return z;
+  }
+};
+
 // The current of cell (i,j,k) of block blk (planes of stride `plane`, interior
 // layout, block at coff), where only coordinate D may lie outside the block:
 // then the face neighbour's cell (its face must exist).

@@ -53,7 +53,8 @@ def partial_blocks(body):
         for _, u, _ in body[at[skip[2]]:]:
             if re.match(r"s_\w+_b64 exec\b|s_\w+_saveexec_b64|s_c?branch|s_endpgm|s_barrier|s_setpc", u):
                 break
-            if re.match(r"(v|ds|global|scratch|buffer|flat)_", u):
+            # v_readlane and v_writelane ignore the mask
+            if re.match(r"(v|ds|global|scratch|buffer|flat)_(?!(read|write)lane)", u):
                 found.append((hex(addr), u))
     return found
 
