@@ -90,8 +90,11 @@ typedef enum { AMRVAC_RK3 = 0, AMRVAC_SSPRK43 = 1, AMRVAC_SSPRK54 = 2 } amrvac_s
  *                   block-size class (blocks of equal cell count; a class
  *                   with fewer tiles than twice the resident work-groups
  *                   joins the next), runs of 8 steps replayed from a HIP
- *                   graph (captured by the first call that long), the
- *                   remainder of a call launched kernel by kernel;
+ *                   graph (captured by the first call that long), calls of
+ *                   one step that return the end time from another (captured
+ *                   by the seventh such call), other steps, and all steps of
+ *                   a stream that the caller is capturing, launched kernel by
+ *                   kernel;
  *  BATCHED_SINGLE:  one persistent fused launch per stage over the whole
  *                   list (each XCD's share holds an eighth of every class),
  *                   steps replayed from HIP graphs as for BATCHED.

@@ -1222,18 +1222,55 @@ static amrvac_status line_steps(amrvac_ctx* c, int scheme, double cfl, const dou
   return AMRVAC_OK;
 }
 
-// Steps per graph: a graph launch costs about 6 us on top of its kernels (2D
-// Euler 256^2, before the stages got shorter: 81 us per step replaying a
-// one-step graph, 75 us launching the kernels one by one, 74 us replaying
-// 8-step graphs), so runs of steps replay 8-step graphs and the remainder of a
-// call is launched kernel by kernel.  The graph is captured by the first call
-// of at least GRAPH_STEPS steps: shorter calls never pay for the capture
-// (0.3 to 0.8 ms of the first call on a new context).
+// Steps per graph: a graph launch costs about 6 us on top of its kernels, where
+// it does not hide behind work already enqueued (2D Euler 256^2, before the
+// stages got shorter: 81 us per step replaying a one-step graph, 75 us launching
+// the kernels one by one, 74 us replaying 8-step graphs), so runs of steps replay
+// 8-step graphs and the remainder of a call is launched kernel by kernel.  The
+// graph is captured by the first call of at least GRAPH_STEPS steps: shorter
+// calls never pay for the capture (0.3 to 0.8 ms of the first call on a new
+// context).
 constexpr int GRAPH_STEPS = 8;
+// A call of one step that returns its time starts on a stream that the call
+// before has waited for.  There a graph launch hides behind the reduction of the
+// initial state, and its kernels follow each other faster than launched one by
+// one: SSPRK(5,4) on 20 blocks of 100 hydro cells 118 -> 106 us a call, 2D Euler
+// on 4 blocks of 16^2 94 -> 83, 3D GLM on 4 of 8^3 149 -> 139.  Programs that
+// step so replay a one-step graph, captured by the call after SINGLE_CALLS
+// others, by when these have lost about what the capture costs (40 to 80 us).
+// Calls that return no time follow each other without a gap, and a graph launch
+// between them costs more than it saves (62.7 against 67.7 us in the first of
+// these cases, 42.9 against 44.2 in the second).
+constexpr int SINGLE_CALLS = 6;
+constexpr int SINGLE_KEY = 16;   // graphs[scheme + SINGLE_KEY]
+
+// Replays the graph of `steps` steps, captured on first use.
+static amrvac_status replay(amrvac_ctx* c, GraphEntry& g, int scheme, int steps) {
+  if (!g.exec) {
+    HIP_TRY(c, hipStreamBeginCapture(c->cap, hipStreamCaptureModeRelaxed));
+    for (int k = 0; k < steps; ++k) enqueue_step(c, scheme, AMRVAC_EXEC_BATCHED, c->cap, 0, 1, 2, 3, 0);
+    hipError_t e = hipStreamEndCapture(c->cap, &g.graph);
+    if (e != hipSuccess) {
+      g.graph = nullptr;
+      return fail(c, AMRVAC_ERR_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
+    }
+    HIP_TRY(c, hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0));
+  }
+  HIP_TRY(c, hipGraphLaunch(g.exec, c->stream));
+  return AMRVAC_OK;
+}
+
+// Whether the caller is capturing the context's stream, into which no graph can
+// be launched.
+static bool capturing(const amrvac_ctx* c) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+  return st != hipStreamCaptureStatusNone;
+}
 
 // The steps of amrvac_ssprk_step on the stage buffers the state tables
 // point at (context scratch, or the fixed array); with use_graph the batched
-// form replays a cached graph of GRAPH_STEPS steps.
+// form replays cached graphs.
 static amrvac_status enqueue_steps(amrvac_ctx* c, int scheme, double cfl, const double* dt_fixed, int nsteps,
                                    double* t_inout, bool use_graph) {
   if (c->var->line && nsteps > 0)
@@ -1250,26 +1287,22 @@ static amrvac_status enqueue_steps(amrvac_ctx* c, int scheme, double cfl, const 
   launch_set_control(c->d_ctl, dt_fixed ? *dt_fixed : 0.0, cfl, t_inout ? *t_inout : 0.0, c->stream);
   if (nsteps > 0) launch_cmax_of(c, 0, 0, c->stream, true);
   const int exec = c->exec;
-  if (use_graph && exec == AMRVAC_EXEC_BATCHED && nsteps > 0) {
-    int it = 0;
-    if (nsteps >= GRAPH_STEPS) {
-      GraphEntry& g = c->graphs[scheme];
-      if (!g.exec) {
-        HIP_TRY(c, hipStreamBeginCapture(c->cap, hipStreamCaptureModeRelaxed));
-        for (int k = 0; k < GRAPH_STEPS; ++k) enqueue_step(c, scheme, exec, c->cap, 0, 1, 2, 3, 0);
-        hipError_t e = hipStreamEndCapture(c->cap, &g.graph);
-        if (e != hipSuccess) {
-          g.graph = nullptr;
-          return fail(c, AMRVAC_ERR_DEVICE, "graph capture failed: %s", hipGetErrorString(e));
-        }
-        HIP_TRY(c, hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0));
+  int it = 0;
+  const bool single = nsteps == 1 && t_inout;
+  if (use_graph && exec == AMRVAC_EXEC_BATCHED && (single || nsteps >= GRAPH_STEPS) && !capturing(c)) {
+    amrvac_status st = AMRVAC_OK;
+    if (single) {
+      GraphEntry& g = c->graphs[scheme + SINGLE_KEY];
+      if (g.exec || ++g.calls > SINGLE_CALLS) {
+        st = replay(c, g, scheme, 1);
+        it = 1;
       }
-      for (; it + GRAPH_STEPS <= nsteps; it += GRAPH_STEPS) HIP_TRY(c, hipGraphLaunch(g.exec, c->stream));
     }
-    for (; it < nsteps; ++it) enqueue_step(c, scheme, exec, c->stream, 0, 1, 2, 3, 0);
-  } else {
-    for (int it = 0; it < nsteps; ++it) enqueue_step(c, scheme, exec, c->stream, 0, 1, 2, 3, 0);
+    for (; it + GRAPH_STEPS <= nsteps && st == AMRVAC_OK; it += GRAPH_STEPS)
+      st = replay(c, c->graphs[scheme], scheme, GRAPH_STEPS);
+    if (st != AMRVAC_OK) return st;
   }
+  for (; it < nsteps; ++it) enqueue_step(c, scheme, exec, c->stream, 0, 1, 2, 3, 0);
   HIP_TRY(c, hipGetLastError());
   return AMRVAC_OK;
 }

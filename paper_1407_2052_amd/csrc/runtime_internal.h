@@ -33,6 +33,7 @@ struct LaunchGroup {
 struct GraphEntry {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
+  int calls = 0;   // before the capture
 };
 
 }  // namespace amrvac
