@@ -1029,13 +1029,17 @@ static StageVariant preferred(StageVariant v) {
 // blocks of 5-39 x 152) 53.7 us with the general form against 55.3.  Of each
 // (ndim, physics, reconstruction) the one marked preferred, else the first,
 // serves where no role-split form does (2D GLM, the same blocks: 101 us, the
-// first shape 152; 1D MHD with LIM03, 60 blocks of 20-399: 33 against 40).
-// WPE = minimum waves per SIMD requested from the register allocator.
+// first shape 152; 1D MHD with LIM03, 60 blocks of 20-399: 33 against 40).  In 1D
+// hydro an SSPRK(5,4) step with MP5 takes 34.4 us on 20 blocks of 100, 56.6 with
+// the first shape, and 36.4 against 47.9 on 65536 cells; one launch per block 394
+// against 414 (RK3).  With LIM03 64 cells a tile take 38.9 against 53.3 us, but
+// one launch per block 431 against 399.  WPE = minimum waves per SIMD requested
+// from the register allocator.
 static const StageVariant g_variants[] = {
     // 1D
     AMRVAC_VARIANT(1, false, 128, 1, 1, 128, 1, 1),
     AMRVAC_VARIANT(1, false, 64, 1, 1, 64, 1, 1),
-    AMRVAC_VARIANT_RC(1, false, 64, 1, 1, 64, 1, 1),
+    preferred(AMRVAC_VARIANT_RC(1, false, 64, 1, 1, 64, 1, 1)),
     AMRVAC_VARIANT(1, true, 128, 1, 1, 128, 1, 1),
     AMRVAC_VARIANT(1, true, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_R(1, true, 64, 1, 1, 64, 1, 1),

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import helpers
-from paper_1407_2052_amd import amrvac as A
+from paper_1407_2052_amd import amrvac as A, inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -82,4 +82,19 @@ def test_a_saved_choice_is_reused(tmp_path, monkeypatch):
     path.write_text(text.replace(name, saved))
     name, ms = ctx.autotune(A.RK3, 1)
     assert name == saved and all(m < 0 for m in ms)
+    ctx.close()
+
+
+@pytest.mark.parametrize("ndim,physics,recon,shape", [
+    (1, A.HD, A.MP5, "1d-false-tile" + CORE1), (1, A.HD, A.LIM03, "1d-false-tile128x1x1-nt128-g1-w1-lim03"),
+    (1, A.MHD, A.MP5, "1d-true-tile128x1x1-nt128-g1-w1"), (1, A.MHD, A.LIM03, "1d-true-tile" + RUNS1 + "-lim03-core"),
+    (2, A.GLM, A.MP5, "2d-glm-tile16x16x1-nt256-g1-w2-runs-rec0-core"),
+    (3, A.GLM, A.MP5, "3d-glm-tile8x8x4-nt256-g1-w2-runs-rec0-core"),
+    (2, A.HD, A.MP5, "2d-false-roles16x8x1-nt256-w4"), (3, A.MHD, A.LIM03, "3d-true-roles8x8x4-nt512-w4-lim03")])
+def test_default_shape(ndim, physics, recon, shape):
+    bs = helpers.strip_blocks(ndim, physics != A.HD, [700, 600] if ndim == 1 else [8, 8], 8, 8, seed=5)
+    if physics == A.GLM:
+        bs = inputs.as_glm(bs)
+    ctx, flat, views = A.context_for(bs, recon=recon)
+    assert ctx.current_variant() == shape
     ctx.close()
