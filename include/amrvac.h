@@ -195,7 +195,9 @@ amrvac_status amrvac_set_exec(amrvac_ctx *ctx, int exec);
  * results are bitwise identical for every shape).  Two kinds of shape do not
  * serve every list: "...-line", the one-launch form of small 1D lists (above),
  * and "...-roles...", for blocks in 2D and 3D whose rows and planes, with ghost
- * layers, are within 2^28 cells (24 n0, plus 12 n0 n1 in 3D).  They are the
+ * layers, are within 2^28 cells (24 n0, plus 12 n0 n1 in 3D; the environment
+ * variable AMRVAC_ROLES_MAX_OFFSET at amrvac_create lowers that bound, for
+ * tests), which amrvac_ssprk_adjoint's recompute uses likewise.  They are the
  * default where they fit; where a chosen one does not, a general shape runs
  * until a list, execution form or active set that it fits is set.
  * amrvac_get_variant returns the index of the shape that runs (-1 for NULL

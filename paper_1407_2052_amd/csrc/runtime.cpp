@@ -150,7 +150,7 @@ static const StageVariant* pick_variant(const amrvac_ctx* c, int want) {
 bool amrvac::offsets_fit(const amrvac_ctx* c) {
   for (const amrvac_block& q : c->hb) {
     const long long s1 = q.n[0] + 2 * NG, s2 = s1 * (q.n[1] + 2 * NG);
-    if ((c->cfg.ndim >= 2 ? 24 * s1 : 0) + (c->cfg.ndim >= 3 ? 12 * s2 : 0) > (1ll << 28)) return false;
+    if ((c->cfg.ndim >= 2 ? 24 * s1 : 0) + (c->cfg.ndim >= 3 ? 12 * s2 : 0) > c->max_offset) return false;
   }
   return true;
 }
@@ -835,6 +835,8 @@ amrvac_status amrvac_create(const amrvac_config* cfg, void* hip_stream, amrvac_c
   c->single_launch = cfg->exec == AMRVAC_EXEC_BATCHED_SINGLE;
   c->nvar = cfg->physics == AMRVAC_GLM ? 9 : cfg->physics == AMRVAC_MHD ? 8 : 2 + cfg->ndim;
   c->stream = (hipStream_t)hip_stream;
+  if (const char* env = std::getenv("AMRVAC_ROLES_MAX_OFFSET"))
+    if (*env) c->max_offset = std::max(0ll, std::min(c->max_offset, std::atoll(env)));
   c->var_index = resolve_variant(c, -1);
   c->var = pick_variant(c, c->var_index);
   hipError_t e = hipGetDevice(&c->device);

@@ -70,6 +70,7 @@ struct amrvac_ctx {
 
   // tiles of the chosen variant
   const StageVariant* var = nullptr;
+  long long max_offset = 1ll << 28;   // cells that a role-split tile's 32-bit offsets reach
   int want = -1;        // the caller's choice of variant, -1: none
   int var_index = 0;    // of var
   std::vector<Tile> htiles;
