@@ -41,3 +41,23 @@ def test_fixed_faces_against_the_oracle(ndim, xs, ny, nz, mhd, recon, scheme):
     worst = max(float(np.abs(g - r).max()) for g, r in zip(got, ref))
     print(f"  max |gpu - oracle| / max |oracle| = {worst / scale:.2e}", flush=True)
     assert worst <= 1e-10 * scale
+
+
+def test_refusal_counts_the_tables():
+    """A checkpoint interval whose stage states cannot fit is refused before
+    anything is allocated, with the tables among the figures: 512 + 16 bytes a
+    tile of the recompute, 448 + 16 + 24 a tile of the VJP, the ghost cells'
+    adjoint, and 24 bytes a stage state for its c_max."""
+    bs = helpers.strip_blocks(3, True, [9] * 256, 9, 5, seed=13, periodic=False)
+    ctx, flat, views = A.context_for(bs)
+    lam = [torch.zeros_like(v) for v in views]
+    free, _ = torch.cuda.mem_get_info()
+    # a stage state: 64 bytes a cell of the slot and 3 code words
+    k = int(1.2 * free / (5 * 256 * 9 * 9 * 5 * (64 + 24)))
+    with pytest.raises(A.AmrvacError) as e:
+        ctx.ssprk_adjoint(A.SSPRK54, 1e-4, k, k, lam)
+    ctx.close()
+    assert e.value.status == A.ERR_NOMEM
+    ghosts = 256 * 2 * 3 * (9 * 5 + 9 * 9) + 2 * 3 * 9 * 5
+    want = 256 * (8 * (512 + 16) + 4 * (448 + 16 + 24)) + 64 * ghosts + 24 * 5 * k
+    assert f"{want / 1e9:.4f} GB of tables" in str(e.value)
