@@ -8,6 +8,15 @@ namespace amrvac {
 constexpr int NG = 3;          // ghost layers (MP5 stencils reach i-2..i+3)
 constexpr int MAX_SLOTS = 8;   // c_max slots per step (stages + 1)
 
+// Radius r of LIM03's asymptotic region, in units of the data per cell width.
+constexpr double LIM03_RADIUS = 1.0;
+
+// LIM03's scale 1 / (r dx)^2 for split fluxes held without their factor 1/2
+// (doubled data), from 0.5 / dx.
+__host__ __device__ inline double lim03_scale(double hidx) {
+  return (hidx * (1.0 / LIM03_RADIUS)) * (hidx * (1.0 / LIM03_RADIUS));
+}
+
 // One block as the kernels see it.
 struct BlockDev {
   double* u;            // caller's padded state (buffer id 0)

@@ -562,9 +562,6 @@ __device__ __forceinline__ double mp5(double a, double b, double c, double d, do
 // LIM03 (Cada & Torrilhon 2009): compact third-order reconstruction with the
 // asymptotic-region switch.
 // ---------------------------------------------------------------------------
-// Radius r of the asymptotic region, in units of the data per cell width.
-constexpr double LIM03_RADIUS = 1.0;
-
 // Interface value at j+1/2 from a = f_{j-1}, b = f_j, c = f_{j+1}; kr =
 // 1 / (r dx)^2 for the cell width dx along the pencil.  With dm = b - a and
 // dp = c - b the value is b + H/2, where

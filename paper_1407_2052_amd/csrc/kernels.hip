@@ -244,8 +244,7 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
       // reconstructions are homogeneous of degree 1, so it is applied once, to
       // the difference of the interface fluxes (a power of two: the same bits).
       const double hidx_d = 0.5 * idx_d;
-      // LIM03's asymptotic-region scale 1 / (r dx_d)^2, for doubled data
-      const double kr = (hidx_d * (1.0 / LIM03_RADIUS)) * (hidx_d * (1.0 / LIM03_RADIUS));
+      const double kr = lim03_scale(hidx_d);
 
       static_for<0, NGRP>([&](auto Gc) {
         constexpr int G = decltype(Gc)::value;

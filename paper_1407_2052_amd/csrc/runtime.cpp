@@ -787,7 +787,7 @@ static amrvac_status build_line(amrvac_ctx* c) {
     }
     // runs of the block's n + 1 interfaces; the last one ends at the last
     // interface
-    const double kr1 = (0.5 * D.inv_dx[0]) * (0.5 * D.inv_dx[0]);
+    const double kr1 = lim03_scale(0.5 * D.inv_dx[0]);
     for (int q = 0; q < n + 1; q += RUN) {
       const int k0 = std::min(q, n + 1 - RUN);
       c->hline_runs.push_back(LineRun{base[b] + k0, ibase[b] + k0, kr1});

@@ -336,7 +336,7 @@ __global__ void __launch_bounds__(NT, WPE) k_tile(StageParams P) {
       __syncthreads();
 
       // B) interface fluxes R(F+) + R(F-): one variable per wavefront
-      const double kr = (hidx_d * (1.0 / LIM03_RADIUS)) * (hidx_d * (1.0 / LIM03_RADIUS));
+      const double kr = lim03_scale(hidx_d);
       constexpr int W = RUN + 2 * HG - 2;
       // codes: 4 bits per interface of the run
       auto reconstruct = [&](const double* f, double* r, unsigned long long& codes) {
