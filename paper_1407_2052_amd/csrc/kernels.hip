@@ -355,9 +355,10 @@ __global__ void __launch_bounds__(NT, WPE) k_stage(StageParams P) {
         __syncthreads();
         // B) interface fluxes for every (variable, interface)
         if constexpr (RUNS) {
-          // one item per (variable, pencil, run of up to 5 interfaces): the
-          // run reads every split flux of its window once and, for MP5,
-          // shares curvatures and curvature limiters between its
+          // one item per (variable, pencil, run of interfaces; up to the whole
+          // pencil by runs_per_pencil, at most 5 with EMIT): the run reads
+          // every split flux of its window once and, for MP5, shares
+          // differences, curvatures and curvature limiters between its
           // interfaces.  The last run of a pencil is shifted back to end at
           // the pencil's last interface.
           constexpr int NIF = S::T(D) + 1;
@@ -756,7 +757,7 @@ __global__ void __launch_bounds__(256) k_cmax(CmaxParams P) {
 #pragma unroll
         for (int d = 0; d < NDIM; ++d) {
           if (__ballot(in && speed_may_exceed<MHD>(w, d, P.gamma, run[d])) != 0)
-            run[d] = fmax(run[d], wave_max(in ? fabs(w.v[d]) + fmax(fast_speed<MHD>(w, d, P.gamma), 0.0) : 0.0));
+            run[d] = fmax(run[d], wave_max(in ? fabs(w.v[d]) + fast_speed<MHD>(w, d, P.gamma) : 0.0));
         }
       }
     }

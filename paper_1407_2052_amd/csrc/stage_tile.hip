@@ -72,7 +72,6 @@ __global__ void __launch_bounds__(64) k_tile_info(const BlockDev* blocks, const 
           if (in_block > 0) s.rem = in_block;
         }
       }
-      if (s.rem == 0) s.rem = hg;
     }
     const int c[3] = {tl.o[0], tl.o[1], tl.o[2]};
     I.side[slot][6] = TileSide{};
