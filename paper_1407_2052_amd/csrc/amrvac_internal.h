@@ -221,13 +221,11 @@ constexpr int LINE_LDS_BYTES = 160 * 1024;
 constexpr int LINE_STEPS = 64;                // steps per launch
 
 // A cell of the list (then the ghost cells of its fixed faces), one per
-// thread: where its state is in the caller's array and in a scratch slot, its
-// entry in the lines of split fluxes and up to two halo entries that repeat it,
-// its lower interface, 0.5 / dx.
+// thread: where its state is, its entry in the lines of split fluxes and up to
+// two halo entries that repeat it, its lower interface, 0.5 / dx.
 struct LineCell {
   double* u;
   long long vs;
-  long long slot, slot_vs;
   double hidx;
   int pos, dup[2], ifc;
 };
@@ -249,7 +247,6 @@ struct LineStage {
 struct LineParams {
   const LineCell* cells;
   const LineRun* runs;
-  double* slot;                 // advance the state in this scratch slot, or null: the caller's arrays
   Control* ctl;
   double gamma, dt_fixed, cfl, t0, dx_min;
   int ncells, nghost, nruns, length, nifc;

@@ -49,13 +49,12 @@ __global__ void __launch_bounds__(line_threads(MHD)) k_line(LineParams P) {
   const bool has = tid < P.ncells + P.nghost;
   const double gamma = P.gamma;
   const LineCell me = P.cells[has ? tid : 0];
-  // fixed ghost cells are in the caller's arrays either way
-  const bool in_slot = P.slot != nullptr && cell;
-  const gptr_w state = (gptr_w)(in_slot ? P.slot + me.slot : me.u);
-  const long long vs = in_slot ? me.slot_vs : me.vs;
   double u[NV], U0[NV], S[NV];
+  {
+    gptr p = (gptr)me.u;
 #pragma unroll
-  for (int v = 0; v < NV; ++v) u[v] = state[v * vs];
+    for (int v = 0; v < NV; ++v) u[v] = p[v * me.vs];
+  }
   bool ok_all = true;
   double ri = 1.0, pr = 1.0;   // 1/rho and p of u
   // c_max of the current state, the same in every thread
@@ -147,8 +146,9 @@ __global__ void __launch_bounds__(line_threads(MHD)) k_line(LineParams P) {
     }
   }
   if (cell) {
+    gptr_w p = (gptr_w)me.u;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) state[v * vs] = u[v];
+    for (int v = 0; v < NV; ++v) p[v * me.vs] = u[v];
   }
   if (tid == 0) {
     P.ctl->t = t;

@@ -770,8 +770,6 @@ static amrvac_status build_line(amrvac_ctx* c) {
       LineCell k{};
       k.u = D.u + (i + NG);
       k.vs = D.P[0];
-      k.slot = D.off + i;
-      k.slot_vs = D.cells;
       k.hidx = 0.5 * D.inv_dx[0];
       k.pos = base[b] + NG + i;
       k.ifc = ibase[b] + i;
@@ -809,7 +807,7 @@ static amrvac_status build_line(amrvac_ctx* c) {
 }
 
 static amrvac_status line_steps(amrvac_ctx* c, int scheme, double cfl, const double* dt_fixed, int nsteps, double t0,
-                                int buf);
+                                const LineCell* cells);
 
 extern "C" {
 
@@ -1030,6 +1028,22 @@ amrvac_status amrvac_autotune(amrvac_ctx* c, int scheme, int nsteps, double* ms_
   // time every shape on scratch copies: slot ids 1..3 = A, B, S; 4 = U copy
   amrvac_status st = ensure_slots(c, 4);
   if (st != AMRVAC_OK) return st;
+  // the one-launch form's cells in slot 4
+  struct LineCopy {
+    LineCell* cells = nullptr;
+    ~LineCopy() { if (cells) (void)hipFree(cells); }
+  } line_copy;
+  if (c->d_line_cells) {
+    std::vector<LineCell> cells = c->hline_cells;
+    size_t k = 0;
+    for (const BlockDev& D : c->hdev)
+      for (int i = 0; i < D.n[0]; ++i, ++k) {
+        cells[k].u = c->d_scr + 3 * c->slot_stride + D.off + i;
+        cells[k].vs = D.cells;
+      }
+    HIP_TRY(c, hipMalloc(&line_copy.cells, sizeof(LineCell) * cells.size()));
+    HIP_TRY(c, hipMemcpy(line_copy.cells, cells.data(), sizeof(LineCell) * cells.size(), hipMemcpyHostToDevice));
+  }
   const int keep = c->want;
   const int keep_exec = c->exec;
   c->exec = AMRVAC_EXEC_BATCHED;
@@ -1047,7 +1061,7 @@ amrvac_status amrvac_autotune(amrvac_ctx* c, int scheme, int nsteps, double* ms_
     launch_set_control(c->d_ctl, 0.0, 0.4, 0.0, c->stream);
     launch_cmax_of(c, 4, 0, c->stream, true);
     auto steps = [&](int n) -> amrvac_status {
-      if (c->var->line) return line_steps(c, scheme, 0.4, nullptr, n, 0.0, 4);
+      if (c->var->line) return line_steps(c, scheme, 0.4, nullptr, n, 0.0, line_copy.cells);
       for (int it = 0; it < n; ++it) enqueue_step(c, scheme, AMRVAC_EXEC_BATCHED, c->stream, 4, 1, 2, 3, 4);
       return AMRVAC_OK;
     };
@@ -1176,15 +1190,12 @@ static amrvac_status check_step_args(amrvac_ctx* c, int scheme, double cfl, cons
   return AMRVAC_OK;
 }
 
-// The steps of a small 1D list, LINE_STEPS per launch, on buffer `buf`.
+// The steps of a small 1D list, LINE_STEPS per launch, on the states that the
+// table `cells` names.
 static amrvac_status line_steps(amrvac_ctx* c, int scheme, double cfl, const double* dt_fixed, int nsteps,
-                                double t0, int buf) {
+                                double t0, const LineCell* cells) {
   LineParams p{};
-  if (buf > 0) {
-    const StateTable st = state_table(c);
-    p.slot = st.scr + (buf - 1) * st.slot_stride;
-  }
-  p.cells = c->d_line_cells;
+  p.cells = cells;
   p.runs = c->d_line_runs;
   p.ctl = c->d_ctl;
   p.gamma = c->cfg.gamma;
@@ -1276,7 +1287,7 @@ static bool capturing(const amrvac_ctx* c) {
 static amrvac_status enqueue_steps(amrvac_ctx* c, int scheme, double cfl, const double* dt_fixed, int nsteps,
                                    double* t_inout, bool use_graph) {
   if (c->var->line && nsteps > 0)
-    return line_steps(c, scheme, cfl, dt_fixed, nsteps, t_inout ? *t_inout : 0.0, 0);
+    return line_steps(c, scheme, cfl, dt_fixed, nsteps, t_inout ? *t_inout : 0.0, c->d_line_cells);
   if (!c->hptiles.empty() && nsteps > 0) {
     // passive blocks: their current state in the stage buffers A and B,
     // which active neighbours read as halo at every stage
