@@ -41,16 +41,24 @@ def kernels(text):
 
 def partial_blocks(body):
     """Vector instructions that run with the lanes of an unsaved narrowing after
-    its end: (address of the narrowing, instruction)."""
+    its end, or after a loop with the lanes (none) that are still in it:
+    (address of the narrowing, instruction)."""
     at = {a: i for i, (a, _, _) in enumerate(body)}
     found = []
     for i, (addr, ins, _) in enumerate(body):
         if not re.match(r"s_(and|andn2)_b64 exec, ", ins):
             continue
-        skip = next((b for b in body[i + 1:i + 4] if b[1].startswith("s_cbranch_execz")), None)
-        if skip is None or skip[2] not in at:
+        k, branch = next(((k, b) for k, b in enumerate(body[i + 1:i + 4], i + 1)
+                          if re.match(r"s_cbranch_exec(n?z)", b[1])), (0, None))
+        if branch is None:
             continue
-        for _, u, _ in body[at[skip[2]]:]:
+        if branch[1].startswith("s_cbranch_execz"):
+            if branch[2] not in at:
+                continue
+            start = at[branch[2]]
+        else:
+            start = k + 1
+        for _, u, _ in body[start:]:
             if re.match(r"s_\w+_b64 exec\b|s_\w+_saveexec_b64|s_c?branch|s_endpgm|s_barrier|s_setpc", u):
                 break
             # v_readlane and v_writelane ignore the mask
