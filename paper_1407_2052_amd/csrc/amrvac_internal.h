@@ -185,7 +185,7 @@ struct StageVariant {
   // before the first such launch
   hipError_t (*line)(bool mhd, bool lim, const LineParams& p, size_t lds, hipStream_t s) = nullptr;
   hipError_t (*prepare_line)(bool mhd, bool lim, int run) = nullptr;
-  bool preferred = false;   // among the general forms (info == 0) of its kind
+  int preferred = 0;   // among the general forms (info == 0) of its kind; 2: in the batched forms only
 };
 
 const StageVariant* tile_variants(int* count);   // stage_tile.hip

@@ -1016,8 +1016,8 @@ static void launch_stage(const StageParams& p, int grid, hipStream_t s) {
    &launch_stage<ND, true, TX, TY, TZ, NT, NGRP, WPE, false, true, (REC == 1), false, true, true>,           \
    #ND "d-hall-tile" #TX "x" #TY "x" #TZ "-nt" #NT "-g" #NGRP "-w" #WPE "-runs-rec" #REC "-core"}
 
-static StageVariant preferred(StageVariant v) {
-  v.preferred = true;
+static StageVariant preferred(StageVariant v, int forms = 1) {
+  v.preferred = forms;
   return v;
 }
 
@@ -1032,8 +1032,9 @@ static StageVariant preferred(StageVariant v) {
 // first shape 152; 1D MHD with LIM03, 60 blocks of 20-399: 33 against 40).  In 1D
 // hydro an SSPRK(5,4) step with MP5 takes 34.4 us on 20 blocks of 100, 56.6 with
 // the first shape, and 36.4 against 47.9 on 65536 cells; one launch per block 394
-// against 414 (RK3).  With LIM03 64 cells a tile take 38.9 against 53.3 us, but
-// one launch per block 431 against 399.  WPE = minimum waves per SIMD requested
+// against 414 (RK3).  With LIM03 64 cells a tile take 38.9 against 53.3 us, 41.5
+// against 44.6 on 65536 cells, but one launch per block 431 against 399, where
+// the first shape stays.  WPE = minimum waves per SIMD requested
 // from the register allocator.
 static const StageVariant g_variants[] = {
     // 1D
@@ -1088,7 +1089,7 @@ static const StageVariant g_variants[] = {
     AMRVAC_VARIANT_LR(3, true, 8, 8, 4, 256, 2, 3),
     AMRVAC_VARIANT_LR(3, true, 8, 8, 8, 512, 2, 4),
     AMRVAC_VARIANT_L(1, false, 128, 1, 1, 128, 1, 1),
-    AMRVAC_VARIANT_L(1, false, 64, 1, 1, 64, 1, 1),
+    preferred(AMRVAC_VARIANT_L(1, false, 64, 1, 1, 64, 1, 1), 2),
     AMRVAC_VARIANT_L(1, true, 128, 1, 1, 128, 1, 1),
     AMRVAC_VARIANT_L(1, true, 64, 1, 1, 64, 1, 1),
     AMRVAC_VARIANT_L(2, false, 16, 16, 1, 256, 1, 1),
@@ -1147,7 +1148,7 @@ const StageVariant* stage_variants(int* count) {
           if (q.ndim == 1 && q.mhd == mhd && q.rec == rec && !q.hall && !q.line)
             if (!base || (q.preferred && !base->preferred)) base = &q;
         StageVariant q = *base;
-        q.preferred = false;
+        q.preferred = 0;
         q.name = names[mhd][rec];
         q.line = launch_line;
         q.prepare_line = prepare_line;

@@ -173,8 +173,8 @@ static int resolve_variant(const amrvac_ctx* c, int want) {
   const int n = count_variants(c);
   int general = 0;
   for (int k = n - 1; k >= 0; --k) {
-    const StageVariant* v = pick_variant(c, k);
-    if (v->preferred) general = k;
+    const int p = pick_variant(c, k)->preferred;
+    if (p == 1 || (p == 2 && c->exec == AMRVAC_EXEC_BATCHED)) general = k;
   }
   if (want < 0) {
     for (int k = 0; k < n; ++k) {

@@ -86,7 +86,7 @@ def test_a_saved_choice_is_reused(tmp_path, monkeypatch):
 
 
 @pytest.mark.parametrize("ndim,physics,recon,shape", [
-    (1, A.HD, A.MP5, "1d-false-tile" + CORE1), (1, A.HD, A.LIM03, "1d-false-tile128x1x1-nt128-g1-w1-lim03"),
+    (1, A.HD, A.MP5, "1d-false-tile" + CORE1), (1, A.HD, A.LIM03, "1d-false-tile64x1x1-nt64-g1-w1-lim03"),
     (1, A.MHD, A.MP5, "1d-true-tile128x1x1-nt128-g1-w1"), (1, A.MHD, A.LIM03, "1d-true-tile" + RUNS1 + "-lim03-core"),
     (2, A.GLM, A.MP5, "2d-glm-tile16x16x1-nt256-g1-w2-runs-rec0-core"),
     (3, A.GLM, A.MP5, "3d-glm-tile8x8x4-nt256-g1-w2-runs-rec0-core"),
@@ -96,5 +96,10 @@ def test_default_shape(ndim, physics, recon, shape):
     if physics == A.GLM:
         bs = inputs.as_glm(bs)
     ctx, flat, views = A.context_for(bs, recon=recon)
+    assert ctx.current_variant() == shape
+    ctx.set_exec(A.EXEC_PER_BLOCK)
+    first = ndim == 1 and physics == A.HD and recon == A.LIM03   # faster there
+    assert ctx.current_variant() == ("1d-false-tile128x1x1-nt128-g1-w1-lim03" if first else shape)
+    ctx.set_exec(A.EXEC_BATCHED)
     assert ctx.current_variant() == shape
     ctx.close()
